@@ -31,7 +31,7 @@ FLAGS = [
     f"-I{os.path.join(ROOT, 'include')}",
 ]
 
-# Per-file flags.  The wave kernel reads a tile-queue atomic's result one tile
+# Per-file flags.  The wave kernel reads its LDS tile counter's atomic one tile
 # after issuing it; the atomic optimizer would turn the single-lane atomic into
 # a wave reduction that reads the result (and waits for it) at once.
 FILE_FLAGS = {

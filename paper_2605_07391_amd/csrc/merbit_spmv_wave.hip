@@ -13,14 +13,28 @@
 //     are added atomically to y, which is zero at every tile's first row before
 //     the launch (dual buffer: each tile zeroes z at its first row, Sec. 4.2
 //     opt. (3)).
-// A block of WAVES wavefronts is resident for the whole launch; wavefront g
-// of the grid takes tiles g, g + W_total, g + 2 W_total, ...  (with the tiles
-// split into ranges, the same within the block's range, over the blocks of
-// that range; with a tile queue, only the first tile is fixed and the rest of
-// the range is handed out one tile at a time).  The loads of the next tile
-// (bounds, descriptor, col_ind, values) are issued before the current tile's
-// gathers are consumed, so memory stays busy while a tile is walked and
-// committed.
+// A block of WAVES wavefronts is resident for the whole launch.  The tiles
+// (with the tiles split into ranges, those of the block's range) are dealt
+// round robin over the blocks, and a block's wavefronts take the block's tiles
+// one at a time from a counter in LDS.  The loads of the next tile (bounds,
+// descriptor, col_ind, values) are issued before the current tile's gathers
+// are consumed, so memory stays busy while a tile is walked and committed.
+//
+// What bounds it: the x gathers (L1 misses in flight per CU times the latency
+// of L2) and, below about 10M nonzeros, the fixed costs (the copy of the hot
+// values, the launch).  Time per tile varies by its columns, and neighbouring
+// tiles are alike, so wavefronts with a fixed sequence of tiles (g, g + W,
+// ...: 16 neighbours per block) ended 30-68 us into a 68 us launch on R-MAT 20
+// FP32 (mean 48).  Dealing single tiles over the blocks and taking them from
+// the block's counter: 39-56 us.  With the walk below, per SpMV: R-MAT 20 70.2
+// -> 60.2 us (FP32), 97.7 -> 90 us (FP64), Chung-Lu 700,001 45.3 -> 38.7 us
+// (FP32), R-MAT 22 on 8 stripes, 64-bit descriptors, sigma 28, 210 -> 196 us
+// (FP32; there it replaces one global counter per range, which cost an atomic
+// round trip per tile).  Deals of 2 or 4 tiles at a time were 1 and 2 %
+// slower; a software pipeline that issues the next tile's gathers before the
+// current walk, and gathers split from the LDS reads (buffer loads, or loads
+// under a branch, where the compiler now merges both into one flat load) made
+// no difference.
 //
 // HOT: the block first copies the hot x values into LDS (the plan's recoded
 // column stream marks hot columns as -1 - slot) and serves those gathers from
@@ -68,9 +82,9 @@ template <typename V>
 constexpr int kHotBatch = 128 / (int)sizeof(V);
 
 // A load through the constant address space: the tile bounds are never
-// written during a launch, and with the tile-queue atomics in the loop the
-// compiler could otherwise not prove that, and would load the (uniform) bounds
-// with vector loads that wait for every gather in flight.
+// written during a launch, and with atomics in the loop the compiler could
+// otherwise not prove that, and would load the (uniform) bounds with vector
+// loads that wait for every gather in flight.
 template <typename T>
 __device__ __forceinline__ T const_load(const T* p, int i) {
   typedef const __attribute__((address_space(4))) T ConstT;
@@ -131,6 +145,12 @@ __device__ __forceinline__ void wave_load_tile(const SpmvArgs& a, const int32_t*
   }
 }
 
+// Steps of the walk whose products are read from LDS together.  4 is the best
+// or level with it everywhere (R-MAT 20 / 22, sigma 7-28); more cost
+// registers: FP64 sigma 20 on R-MAT 22 took 291 / 302 / 309 us per SpMV at 4 /
+// 8 / 20 steps.
+constexpr int kWalkGroup = 4;
+
 template <typename V, int SIGMA, int WAVES, bool HOT, typename D>
 __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
   constexpr int BITS = ceil_log2(kOmega * SIGMA);
@@ -138,6 +158,7 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
   static_assert(2 * BITS + SIGMA <= 8 * (int)sizeof(D), "descriptor does not fit");
   constexpr int WLDS = kOmega * SIGMA;  // per wavefront: products, then inner-row slots
   __shared__ V s_stage[WAVES * WLDS];
+  __shared__ int s_next;  // the block's next tile (its place in the block's sequence)
 
   const int32_t* __restrict__ col = a.col;
   const V* __restrict__ val = static_cast<const V*>(a.val);
@@ -154,10 +175,8 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
   // the plan splits the tiles into ranges)
   int t_begin = 0, t_end = a.tile_num, slot = blockIdx.x, slots = a.grid;
   int h_begin = 0, h_num = a.hot_n;
-  unsigned long long* queue = a.queue;
   if (a.ranges > 1) {
     const int k = blockIdx.x % a.ranges;
-    if (queue) queue += kQueueStride * k;
     t_begin = a.range_tile[k];
     t_end = a.range_tile[k + 1];
     slot = blockIdx.x / a.ranges;
@@ -168,6 +187,7 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
     }
   }
 
+  if (tid == 0) s_next = WAVES;
   extern __shared__ __align__(16) unsigned char s_dyn[];
   const V* s_hot = reinterpret_cast<const V*>(s_dyn);
   if (HOT) {
@@ -196,33 +216,28 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
         if (s < h_num) dst[s] = hv[u];
       }
     }
-    __syncthreads();
   }
+  __syncthreads();
 
-  // Every wavefront of the range first takes one tile of the range's first
-  // slots * WAVES; further tiles come from the range's queue counter, one at a
-  // time, so wavefronts that meet cheap tiles take more of them (without a
-  // queue: the fixed sequence t + stride, t + 2 stride, ...).  The number of
-  // the tile after next is requested while the current tile is worked on and
-  // read at the end of it: the atomic's latency hides behind a tile, and
-  // waiting for it (memory returns in issue order) never waits for loads the
-  // next iteration does not need first anyway.
-  const int stride = slots * WAVES;
+  // The range's tiles are dealt round robin over its blocks, and the block's
+  // wavefronts take the block's tiles one at a time from a counter in LDS, so
+  // a wavefront that meets cheap tiles takes more of them.
   auto take = [&]() -> int {
     int q = 0;
-    if (lid == 0) q = (int)atomicAdd(queue, 1ull);
+    if (lid == 0) q = atomicAdd(&s_next, 1);
     return q;
   };
-  auto tile_of = [&](int q) -> int {
-    q = __builtin_amdgcn_readfirstlane(q);
-    return q < t_end - t_begin - stride ? t_begin + stride + q : t_end;
+  auto tile_at = [&](int i) -> int {
+    i = __builtin_amdgcn_readfirstlane(i);
+    const int tile = t_begin + i * slots + slot;
+    return tile < t_end ? tile : t_end;
   };
-  int t = t_begin + slot * WAVES + wid;
+  int t = tile_at(wid);
   int tn = t_end;
   WaveTile<V, SIGMA, D> cur;
   if (t < t_end) {
     wave_load_tile<V, SIGMA, D>(a, col, val, t, lid, cur);
-    tn = queue ? tile_of(take()) : t + stride;
+    tn = tile_at(take());
   }
   while (t < t_end) {
     // gathers of the current tile (none for a tile without nonzeros: x may be
@@ -242,8 +257,8 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
     }
     // the tile after next, then the loads of the next tile: both go out
     // before the gathers are consumed
-    int qn = 0;
-    if (queue && tn < t_end) qn = take();
+    int q = 0;
+    if (tn < t_end) q = take();
     WaveTile<V, SIGMA, D> nxt;
     if (tn < t_end) wave_load_tile<V, SIGMA, D>(a, col, val, tn, lid, nxt);
 
@@ -269,31 +284,56 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
         if (k < x_se) s_w[k] = cur.vv[it] * g[it];
       }
       wave_lds_sync();
-      // walk (Algorithm tile_normal_tackle); inner row r (y_ws < r < y_we)
-      // goes to slot x_se + (r - y_ws - 1)
+      // walk (Algorithm tile_normal_tackle): the row that ends at a down step
+      // is written to slot x_se + (its index in the tile), which no other lane
+      // writes.  A lane's right steps read consecutive products, so with xo
+      // the next product and C = x_off + y_off of the lane, step k's product
+      // is s_w[xo] and its row's slot x_se + C + k - xo: neither needs a
+      // product's value, so the reads of a group of steps go out together (one
+      // read at a time, each waited for before the next step, took 4,200 cycles
+      // per tile at sigma 12 against 3,300).
       const int j = t * kOmega + lid;
-      V sum = V(0), first_sum = V(0);
-      bool has_down = false;
-      int start_off = 0;
-      if (j < a.lane_num) {
-        int xo = (int)(cur.desc & FMASK);
-        int yo = (int)((cur.desc >> BITS) & FMASK);
-        start_off = yo;
-        const D flags = cur.desc >> (2 * BITS);
-        const int steps = min(SIGMA, a.path_len - j * SIGMA);
+      V sum = V(0);
+      const int start_off = (int)((cur.desc >> BITS) & FMASK);
+      const D flags = cur.desc >> (2 * BITS);
+      bool has_down = flags != 0;
+      int xo = (int)(cur.desc & FMASK);
+      const int sb = x_se + xo + start_off;
+      if (t < a.tile_num - 1) {
 #pragma unroll
-        for (int k = 0; k < SIGMA; ++k) {
-          if (k < steps) {
-            if ((flags >> k) & 1) {
-              if (has_down) s_w[x_se + yo - 1] = sum;
-              else first_sum = sum;
-              has_down = true;
-              sum = V(0);
-              ++yo;
-            } else {
-              sum += s_w[xo];
-              ++xo;
+        for (int k0 = 0; k0 < SIGMA; k0 += kWalkGroup) {
+          V v[kWalkGroup];
+          int at[kWalkGroup];
+#pragma unroll
+          for (int u = 0; u < kWalkGroup; ++u) {
+            const int k = k0 + u;
+            if (k < SIGMA) {
+              at[u] = xo;
+              v[u] = s_w[xo];
+              xo += (int)((~flags >> k) & 1);
             }
+          }
+#pragma unroll
+          for (int u = 0; u < kWalkGroup; ++u) {
+            const int k = k0 + u;
+            if (k < SIGMA) {
+              const bool down = (flags >> k) & 1;
+              if (down) s_w[sb + k - at[u]] = sum;
+              sum = down ? V(0) : sum + v[u];
+            }
+          }
+        }
+      } else {
+        // the last tile: lanes past the path take no step
+        has_down = has_down && j < a.lane_num;
+        const int steps = min(SIGMA, a.path_len - j * SIGMA);
+#pragma unroll 1
+        for (int k = 0; k < steps; ++k) {
+          if ((flags >> k) & 1) {
+            s_w[sb + k - xo] = sum;
+            sum = V(0);
+          } else {
+            sum += s_w[xo++];
           }
         }
       }
@@ -303,29 +343,22 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
       const V scan = wave_segmented_scan(sum, lid, seg);
       const V carry = dpp_move<kWaveShr1, 0xF>(scan);
       if (has_down) {
-        const V row_val = first_sum + (lid > 0 ? carry : V(0));
+        // the first row that ends in this lane may begin in lanes before it
+        V* slot = s_w + x_se + start_off;
+        const V row_val = *slot + (lid > 0 ? carry : V(0));
         if (start_off == 0) global_add(&y[y_ws], row_val);  // the tile's first row
-        else s_w[x_se + start_off - 1] = row_val;           // begun inside the tile
+        else *slot = row_val;                               // begun inside the tile
       }
       // the last segment belongs to the row the tile ends in
       if (lid == kOmega - 1 && y_we < a.n_rows && scan != V(0)) global_add(&y[y_we], scan);
       wave_lds_sync();
-      for (int r = lid; r < y_we - y_ws - 1; r += kOmega) y[y_ws + 1 + r] = s_w[x_se + r];
+      for (int r = lid + 1; r < y_we - y_ws; r += kOmega) y[y_ws + r] = s_w[x_se + r];
     }
     if (z != nullptr && lid == 0) z[y_ws] = V(0);
     if (tn >= t_end) break;
     cur = nxt;
     t = tn;
-    tn = queue ? tile_of(qn) : tn + stride;
-  }
-  // The range's last wavefront to finish sets its counters back to zero for
-  // the next launch: every other wavefront of the range has taken its last
-  // tile number (and waited for it) before it counts itself finished.
-  if (queue && lid == 0) {
-    if (atomicAdd(queue + 1, 1ull) == (unsigned long long)(stride - 1)) {
-      atomicExch(queue, 0ull);
-      atomicExch(queue + 1, 0ull);
-    }
+    tn = tile_at(q);
   }
 }
 
