@@ -261,10 +261,10 @@ int merbit_pagerank_noalloc(merbit_plan* plan, double alpha, double tol, int max
 /* Y <- A X for k right-hand sides on the same plan (each column is the SpMV
  * of Sec. 4.2).  X: device [n_cols][ldx] row-major (first k columns used),
  * Y: device [n_rows][ldy] row-major, overwritten whatever it held; plan dtype;
- * k >= 1, ldx >= k, ldy >= k; X and Y not aliased.  One wavefront walks one
- * tile of the merge path and its lanes carry the columns of a slab, so every
- * X access is one coalesced read of a row's slab; the columns run in slabs of
- * 32, one launch each (faster than one 64-column launch, FP32 and FP64).
+ * k >= 1, ldx >= k, ldy >= k; X and Y not aliased.  One wavefront takes one
+ * tile of the merge path; groups of its lanes carry the columns of a slab, so
+ * every X access is one coalesced read of a row's slab; the columns run in
+ * slabs of 32, one launch each.
  * Launches: a scatter that zeroes Y at every tile's first row, then the SpMM
  * kernel once per slab. */
 int merbit_spmm(merbit_plan* plan, const void* X, int64_t ldx, void* Y, int64_t ldy, int k,

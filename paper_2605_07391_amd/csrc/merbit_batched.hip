@@ -3,264 +3,225 @@
 // per-graph PageRank update for many graphs stored on the diagonal of one
 // matrix.
 //
-// SpMM (one wavefront per tile, lanes = right-hand-side columns of a slab;
-// the driver runs one launch per slab of 32 columns).  The
-// tile's merge-path segment (Sec. 4.1) fixes its nonzeros [x_ws, x_we) and
-// rows [y_ws, y_we]; every nonzero is a 64-wide row operation
-// Y[row, :] += v * X[col, :], so each X access is one coalesced row load.
-//   1. each lane decodes its descriptor (Sec. 4.1.1) and writes, for each of
-//      its right steps, the row (relative to the tile) of that nonzero into
-//      LDS: nonzero x_off + r of lane j lies in row y_off + (downs before it);
-//   2. the tile's nonzeros are taken 64 at a time, lane l holding nonzero
-//      q0 + l (coalesced loads of col_ind / values, its row from LDS, the
-//      byte offset of its X row); one ballot marks the nonzeros that start a
-//      new row;
-//   3. the wavefront then walks those 64 nonzeros in order: each X row load
-//      takes its offset from the owning lane (a lane read into a scalar
-//      register, used as the buffer load's scalar offset), kSpmmGroup rows
-//      are in flight before the first is used, each product is one fused
-//      multiply-add with the value read from its lane, and a marked nonzero
-//      first finishes the previous row.
-// Per nonzero the wavefront spends one load and a few lane reads, not an
-// LDS round trip, so the X row loads (the bulk of the traffic) stay
-// back to back.  Rows strictly inside the tile are stored; the tile's first
-// and last rows (shared with neighbouring tiles) are added atomically to Y,
-// which is zero there before the launch.  Empty rows inside the tile are
-// written as 0.
+// SpMM (one wavefront per tile; the driver runs one launch per slab of 32
+// columns).  The tile's merge-path segment (Sec. 4.1) fixes its nonzeros
+// [x_ws, x_we) and rows [y_ws, y_we]; every nonzero is a row operation
+// Y[row, :] += v * X[col, :].  The wavefront is cut into groups of KP lanes,
+// KP the power of two that holds the slab's columns, and each group takes an
+// equal run of the tile's nonzeros, its lanes the columns:
+//   1. the tile's values, X row offsets and rows (decoded from the lane
+//      descriptors, Sec. 4.1.1) go to LDS;
+//   2. each group walks its run, kSpmmUnroll X rows in flight before the first
+//      is used; a row that begins and ends inside the run is complete, the
+//      run's first and last rows are not;
+//   3. a head-flagged segmented scan over the groups completes those;
+//   4. the empty rows inside the tile are written as 0.
+// Rows strictly inside the tile are stored; the tile's first and last rows
+// (shared with neighbouring tiles) are added atomically to Y, which is zero
+// there before the launch.
+//
+// What bounds it: with 17 to 32 columns on large graphs the X row reads that
+// miss L2 (R-MAT 20, 32 columns, FP32: 2 GB of them in 284 us); below that the
+// instructions per nonzero, which the groups divide by 64 / KP.  A wavefront
+// that walks one nonzero at a time, its idle lanes repeating the last column,
+// takes as long for 1 column as for 32: R-MAT 18 FP32, 1 / 5 / 16 / 32
+// columns 102 / 102 / 102 / 103 us, now 40 / 51 / 64 / 95; FP64 153 / 153 /
+// 154 / 158, now 45 / 56 / 63 / 106; Chung-Lu 100,003 FP64, 5 columns 49.0,
+// now 21.0.  sigma is an argument, not a template parameter: only the staging
+// loops depend on it.
 #include "merbit_internal.hpp"
 
 namespace merbit {
 
 constexpr int kSpmmWaves = 4;
-constexpr int kSpmmGroup = 16;
-
-template <typename V>
-__device__ __forceinline__ void spmm_commit(V* Y, int64_t ld, int row_abs, int rel, int last_rel,
-                                            int n_rows, V acc, bool lane_on, int lid) {
-  if (!lane_on) return;
-  V* p = Y + (int64_t)row_abs * ld + lid;
-  if (rel == 0 || rel == last_rel) {
-    if (row_abs < n_rows) global_add(p, acc);  // shared with a neighbouring tile
-  } else {
-    __builtin_nontemporal_store(acc, p);  // written once, not read here again
-  }
-}
+// X rows in flight per group before the first is used (R-MAT 18 FP32, 32
+// columns: 129 / 105 / 95 us at 4 / 8 / 16)
+constexpr int kSpmmUnroll = 16;
+// word 3 of a raw (unformatted, stride 0) buffer resource on gfx950
+constexpr int kSpmmBufferWord3 = 0x00020000;
 
 // Per-lane state of a fused personalised-PageRank step (SpmmArgs::Xn).
 template <typename V>
 struct PprRow {
   V* Xn;
   int64_t ld;
-  V a;          // alpha
-  V tele;       // alpha delta_j + 1 - alpha, added at the column's source row
-  int sj;       // the column's source row (-1: lane past the slab)
-  int w0;       // dmask word of the tile's first row
-  uint32_t dm;  // lane l: dmask word w0 + l (the tile's rows are < 32 words)
-  double dsum;  // dangling mass of the rows this lane finished
+  V a;                 // alpha
+  V tele;              // alpha delta_j + 1 - alpha, added at the column's source row
+  int sj;              // the column's source row (-1: lane past the slab)
+  int w0;              // dmask word of the tile's first row
+  const uint32_t* dm;  // the tile's dmask words (LDS)
+  double dsum;         // dangling mass of the rows this lane finished
 };
 
-// Row row_abs, strictly inside the tile, is complete: its next iterate
-// value, written here instead of Y (called by the whole wavefront).
+// Column j of row row_abs (rel within the tile) is complete.  The tile's
+// first and last rows are shared with neighbouring tiles and are added to Y;
+// the others are stored, or with FUSE finished as the next iterate.
+template <typename V, bool FUSE>
+__device__ __forceinline__ void spmm_row(const SpmmArgs& a, int j, int y_ws, int rel,
+                                         int last_rel, V acc, PprRow<V>& f) {
+  const int row = y_ws + rel;
+  V* y = static_cast<V*>(a.Y) + (int64_t)row * a.ldy + j;
+  if (rel == 0 || rel == last_rel) {
+    if (row < a.n_rows) global_add(y, acc);
+  } else if constexpr (FUSE) {
+    V xn = f.a * acc;
+    if (row == f.sj) xn += f.tele;
+    __builtin_nontemporal_store(xn, f.Xn + (int64_t)row * f.ld + j);
+    if ((f.dm[(row >> 5) - f.w0] >> (row & 31)) & 1u) f.dsum += (double)xn;
+  } else {
+    __builtin_nontemporal_store(acc, y);  // written once, not read here again
+  }
+}
+
+// LDS bytes of one wavefront: the tile's values, X row offsets, rows and the
+// marks of its non-empty rows, and (fused step) its dmask words.
 template <typename V>
-__device__ __forceinline__ void ppr_finish_row(PprRow<V>& f, int row_abs, V acc, bool lane_on,
-                                               int lid) {
-  V xn = f.a * acc;
-  if (row_abs == f.sj) xn += f.tele;
-  if (lane_on) __builtin_nontemporal_store(xn, f.Xn + (int64_t)row_abs * f.ld + lid);
-  const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)f.dm, (row_abs >> 5) - f.w0);
-  if ((word >> (row_abs & 31)) & 1u) f.dsum += (double)xn;
+static __host__ __device__ constexpr int spmm_wave_lds(int sigma) {
+  return kOmega * sigma * ((int)sizeof(V) + 4 + 2 + 1) + kOmega * 4;
 }
 
-// A finished row of the tile: the first and last rows go to Y (shared with
-// neighbouring tiles); the others are stored (plain SpMM) or finished as
-// the next iterate (fused step).  Called by the whole wavefront.
-template <typename V, bool FUSE>
-__device__ __forceinline__ void spmm_row(V* Y, int64_t ld, int row_abs, int rel, int last_rel,
-                                         int n_rows, V acc, bool lane_on, int lid,
-                                         PprRow<V>& f) {
-  if constexpr (FUSE) {
-    if (rel == 0 || rel == last_rel) {
-      if (lane_on && row_abs < n_rows) global_add(Y + (int64_t)row_abs * ld + lid, acc);
-    } else {
-      ppr_finish_row(f, row_abs, acc, lane_on, lid);
-    }
-  } else {
-    spmm_commit(Y, ld, row_abs, rel, last_rel, n_rows, acc, lane_on, lid);
-  }
-}
-
-// An empty row strictly inside the tile.
-template <typename V, bool FUSE>
-__device__ __forceinline__ void spmm_empty_row(V* Y, int64_t ld, int row_abs, bool lane_on,
-                                               int lid, PprRow<V>& f) {
-  if constexpr (FUSE) {
-    ppr_finish_row(f, row_abs, V(0), lane_on, lid);
-  } else {
-    if (lane_on) Y[(int64_t)row_abs * ld + lid] = V(0);
-  }
-}
-
-// value of lane `lane` of v (lane uniform), in scalar registers
-__device__ __forceinline__ int lane_value(int v, int lane) {
-  return __builtin_amdgcn_readlane(v, lane);
-}
-__device__ __forceinline__ float lane_value(float v, int lane) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-}
-
-// word 3 of a raw (unformatted, stride 0) buffer resource on gfx950
-constexpr int kSpmmBufferWord3 = 0x00020000;
-
-// One X row element per lane for the nonzero held by lane q of this chunk:
-// through a buffer resource with the row's byte offset as the scalar offset
-// (X no larger than 2 GiB), or through a 64-bit scalar row address.
-// Every lane loads (no branch, so the group's loads go out back to back):
-// lanes at or past k read the row's element k - 1 again (the same line, so a
-// slab narrower than 64 columns fetches no part of X it does not use), and
-// their values are never stored.
-template <typename V, bool BUF>
-__device__ __forceinline__ V load_x_row(__amdgpu_buffer_rsrc_t rx, const V* __restrict__ X,
-                                        int64_t ldx, uint32_t off_l, int c_l, int q, int lane) {
-  if constexpr (BUF) {
-    const int soff = __builtin_amdgcn_readlane((int)off_l, q);
-    if constexpr (sizeof(V) == 4)
-      return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(rx, lane * 4, soff, 0));
-    else
-      return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rx, lane * 8, soff, 0));
-  } else {
-    const V* __restrict__ xr = X + (int64_t)lane_value(c_l, q) * ldx;
-    return xr[lane];
-  }
-}
-
-template <typename V, int SIGMA, bool BUF, bool FUSE>
-__device__ __forceinline__ void spmm_walk(const SpmmArgs& a, const int32_t* __restrict__ wrow,
-                                          int x_ws, int x_se, int y_ws, int last_rel, int lid,
-                                          bool lane_on, V& acc, int& cur, PprRow<V>& f) {
-  const V* __restrict__ X = static_cast<const V*>(a.X);
-  V* __restrict__ Y = static_cast<V*>(a.Y);
-  const int32_t* __restrict__ col = a.col + x_ws;
-  const V* __restrict__ val = static_cast<const V*>(a.val) + x_ws;
-  const int64_t ldx = a.ldx, ldy = a.ldy;
-  // (unused by the 64-bit path)
-  const int bytes = BUF ? (int)((((int64_t)a.x_rows - 1) * ldx + a.k) * (int64_t)sizeof(V)) : 0;
-  const __amdgpu_buffer_rsrc_t rx =
-      __builtin_amdgcn_make_buffer_rsrc((void*)X, (short)0, bytes, kSpmmBufferWord3);
-  const uint32_t row_bytes = (uint32_t)(ldx * (int64_t)sizeof(V));
-  // lanes past k stay on the slab's last column
-  const int lane = min(lid, a.k - 1);
-  for (int q0 = 0; q0 < x_se; q0 += kOmega) {
-    const int ql = q0 + lid;
-    const bool valid = ql < x_se;
-    // the matrix stream is read once: non-temporal, so it does not push the
-    // reused X rows out of L2
-    const int c_l = valid ? __builtin_nontemporal_load(col + ql) : 0;
-    const V v_l = valid ? __builtin_nontemporal_load(val + ql) : V(0);
-    const int r_l = valid ? wrow[ql] : 0;
-    const uint32_t off_l = (uint32_t)c_l * row_bytes;
-    // bit l: nonzero q0 + l lies in another row than the nonzero before it
-    // (every lane takes part in the shuffle: a lane outside it gives no value)
-    const int up = __shfl_up(r_l, 1, kOmega);
-    const int prev = lid == 0 ? cur : up;
-    const unsigned long long starts = __ballot(valid && r_l != prev);
-    const int cnt = min(kOmega, x_se - q0);
-    for (int u0 = 0; u0 < cnt; u0 += kSpmmGroup) {
-      V xr[kSpmmGroup];
-#pragma unroll
-      for (int u = 0; u < kSpmmGroup; ++u) {
-        const int q = min(u0 + u, cnt - 1);  // past the end: a repeat, never used
-        xr[u] = load_x_row<V, BUF>(rx, X, ldx, off_l, c_l, q, lane);
-      }
-#pragma unroll
-      for (int u = 0; u < kSpmmGroup; ++u) {
-        const int q = u0 + u;
-        if (q < cnt) {
-          if ((starts >> q) & 1ull) {
-            const int r = lane_value(r_l, q);
-            spmm_row<V, FUSE>(Y, ldy, y_ws + cur, cur, last_rel, a.n_rows, acc, lane_on, lid, f);
-            for (int e = cur + 1; e < r; ++e)  // empty rows strictly inside the tile
-              spmm_empty_row<V, FUSE>(Y, ldy, y_ws + e, lane_on, lid, f);
-            cur = r;
-            acc = V(0);
-          }
-          acc += lane_value(v_l, q) * xr[u];
-        }
-      }
-    }
-  }
-}
-
-template <typename V, int SIGMA, bool FUSE>
-__global__ __launch_bounds__(kSpmmWaves * 64) void spmm_kernel(SpmmArgs a) {
-  constexpr int WLDS = kOmega * SIGMA;
-  __shared__ int32_t s_row[kSpmmWaves * WLDS];
-
+template <typename V, int KP, bool FUSE>
+__global__ __launch_bounds__(kSpmmWaves * 64) void spmm_kernel(SpmmArgs a, int sigma) {
+  constexpr int G = kOmega / KP;  // groups of KP lanes
+  constexpr int U = kSpmmUnroll;
+  extern __shared__ __align__(16) unsigned char s_dyn[];
   const int lid = threadIdx.x & (kOmega - 1);
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kOmega);
+  const int g = lid / KP, j = lid % KP;
   const int t = blockIdx.x * kSpmmWaves + wid;
-  const bool lane_on = lid < a.k;
+  const bool on = j < a.k;
   PprRow<V> f{};
   if constexpr (FUSE) {
     f.Xn = static_cast<V*>(a.Xn);
     f.ld = a.ldx;
     f.a = (V)a.alpha;
-    f.sj = lane_on ? a.src[lid] : -1;
-    f.tele = lane_on ? (V)(a.alpha * a.sums_in[2 * lid] + 1.0 - a.alpha) : V(0);
+    f.sj = on ? a.src[j] : -1;
+    f.tele = on ? (V)(a.alpha * a.sums_in[2 * j] + 1.0 - a.alpha) : V(0);
     f.dsum = 0.0;
   }
-  // without the fused step no block-wide synchronisation follows: a
-  // wavefront past the last tile may leave at once
   if (t < a.tile_num) {
-    int32_t* wrow = s_row + wid * WLDS;
-    V* __restrict__ Y = static_cast<V*>(a.Y);
+    const int T = kOmega * sigma;
+    unsigned char* lds = s_dyn + wid * spmm_wave_lds<V>(sigma);
+    V* s_val = reinterpret_cast<V*>(lds);
+    uint32_t* s_off = reinterpret_cast<uint32_t*>(s_val + T);
+    uint32_t* s_dm = s_off + T;
+    uint16_t* s_row = reinterpret_cast<uint16_t*>(s_dm + kOmega);
+    unsigned char* s_has = reinterpret_cast<unsigned char*>(s_row + T);
+
     const int x_ws = a.tile_x[t];
     const int x_se = a.tile_x[t + 1] - x_ws;
     const uint32_t tyw = a.tile_y[t];
     const int y_ws = (int)(tyw & kRowMask);
-    const int y_we = (int)(a.tile_y[t + 1] & kRowMask);
-    const int last_rel = y_we - y_ws;
-    if constexpr (FUSE) {
-      // the tile's rows y_ws .. y_we span at most 64 sigma / 32 + 2 words
-      f.w0 = y_ws >> 5;
-      f.dm = f.w0 + lid < a.dmask_words ? a.dmask[f.w0 + lid] : 0u;
-    }
+    const int last_rel = (int)(a.tile_y[t + 1] & kRowMask) - y_ws;
+    const V* __restrict__ X = static_cast<const V*>(a.X);
+    const uint32_t row_bytes = (uint32_t)(a.ldx * (int64_t)sizeof(V));
+    const bool buf = a.x_rows * a.ldx * (int64_t)sizeof(V) < ((int64_t)1 << 31);
 
-    tile_nz_rows<SIGMA>(a.lane_desc, a.lane_num, a.path_len, t, tyw, x_se, lid, wrow);
+    // 1. the tile into LDS.  The matrix stream is read once: non-temporal, so
+    // it does not push the reused X rows out of L2.
+    for (int q = lid; q < x_se; q += kOmega) {
+      const int c = __builtin_nontemporal_load(a.col + x_ws + q);
+      s_val[q] = __builtin_nontemporal_load(static_cast<const V*>(a.val) + x_ws + q);
+      s_off[q] = buf ? (uint32_t)c * row_bytes : (uint32_t)c;
+    }
+    for (int q = lid; q < T / 4; q += kOmega) reinterpret_cast<uint32_t*>(s_has)[q] = 0u;
+    if constexpr (FUSE) {
+      // the tile's rows y_ws .. y_ws + last_rel span at most 2 sigma + 2 words
+      f.w0 = y_ws >> 5;
+      f.dm = s_dm;
+      s_dm[lid] = f.w0 + lid < a.dmask_words ? a.dmask[f.w0 + lid] : 0u;
+    }
+    tile_nz_rows(a.lane_desc, a.lane_num, a.path_len, sigma, t, tyw, x_se, lid, s_row);
+    wave_lds_sync();
+    for (int q = lid; q < x_se; q += kOmega) s_has[s_row[q]] = 1;
     wave_lds_sync();
 
-    V acc = V(0);
-    int cur = 0;  // current row, relative to y_ws
-    const bool buf = ((int64_t)a.x_rows * a.ldx) * (int64_t)sizeof(V) < ((int64_t)1 << 31);
-    if (buf)
-      spmm_walk<V, SIGMA, true, FUSE>(a, wrow, x_ws, x_se, y_ws, last_rel, lid, lane_on, acc,
-                                      cur, f);
-    else
-      spmm_walk<V, SIGMA, false, FUSE>(a, wrow, x_ws, x_se, y_ws, last_rel, lid, lane_on, acc,
-                                       cur, f);
-    const int64_t ldy = a.ldy;
-    if (x_se > 0)
-      spmm_row<V, FUSE>(Y, ldy, y_ws + cur, cur, last_rel, a.n_rows, acc, lane_on, lid, f);
-    // rows after the last nonzero and strictly inside the tile are empty
-    for (int e = (x_se > 0 ? cur + 1 : 1); e < last_rel; ++e)
-      spmm_empty_row<V, FUSE>(Y, ldy, y_ws + e, lane_on, lid, f);
-    if (a.Z != nullptr && lane_on)
-      static_cast<V*>(a.Z)[(int64_t)y_ws * a.ldz + lid] = V(0);
+    // 2. group g walks nonzeros [g L, (g + 1) L), its lanes the columns.  cur
+    // is the row of the nonzero before them: the first row change ends a row
+    // that groups before this one may have begun, so its sum waits in `first`
+    // for their carry; every later row is complete.
+    const int L = ((x_se + G - 1) / G + U - 1) / U * U;
+    const int q0 = g * L;
+    const int cnt = min(max(x_se - q0, 0), L);
+    int cur0 = 0, cur = 0;
+    bool has = false;
+    V acc = V(0), first = V(0);
+    if (cnt > 0) cur0 = cur = s_row[q0 > 0 ? q0 - 1 : 0];
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)X, (short)0,
+        buf ? (int)(((a.x_rows - 1) * a.ldx + a.k) * (int64_t)sizeof(V)) : 0, kSpmmBufferWord3);
+    const int jx = min(j, a.k - 1);  // lanes past k read the row's last column again
+    auto walk = [&](auto load) {
+      for (int i = 0; i < cnt; i += U) {
+        uint32_t off[U];
+        V v[U], x[U];
+        uint16_t r[U];
+        const int q = q0 + i;  // a multiple of U: aligned vector reads
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          off[u] = s_off[q + u];
+          v[u] = s_val[q + u];
+          r[u] = s_row[q + u];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = load(i + u < cnt ? off[u] : off[0]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (i + u < cnt) {
+            if ((int)r[u] != cur) {
+              if (!has) first = acc;
+              else if (on) spmm_row<V, FUSE>(a, j, y_ws, cur, last_rel, acc, f);
+              has = true;
+              cur = r[u];
+              acc = V(0);
+            }
+            acc += v[u] * x[u];
+          }
+        }
+      }
+    };
+    if (buf) {
+      walk([&](uint32_t off) -> V {
+        if constexpr (sizeof(V) == 4)
+          return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(rx, off + jx * 4, 0, 0));
+        else
+          return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rx, off + jx * 8, 0, 0));
+      });
+    } else {
+      walk([&](uint32_t c) -> V { return X[(int64_t)c * a.ldx + jx]; });
+    }
+    // 3. the groups' carries: a segmented scan over the groups of a column
+    V sum = acc;
+    int head = has;
+#pragma unroll
+    for (int d = KP; d < kOmega; d <<= 1) {
+      const V ts = __shfl_up(sum, d, kOmega);
+      const int th = __shfl_up(head, d, kOmega);
+      if (lid >= d) {
+        if (!head) sum += ts;
+        head |= th;
+      }
+    }
+    const V below = __shfl_up(sum, KP, kOmega);
+    if (has && on)
+      spmm_row<V, FUSE>(a, j, y_ws, cur0, last_rel, first + (g > 0 ? below : V(0)), f);
+    if (x_se > 0 && g == G - 1 && on)
+      spmm_row<V, FUSE>(a, j, y_ws, s_row[x_se - 1], last_rel, sum, f);
+    // 4. the empty rows strictly inside the tile
+    for (int e = 1 + g; e < last_rel; e += G)
+      if (!s_has[e] && on) spmm_row<V, FUSE>(a, j, y_ws, e, last_rel, V(0), f);
+    if (a.Z != nullptr && g == 0 && on)
+      static_cast<V*>(a.Z)[(int64_t)y_ws * a.ldz + j] = V(0);
   }
   if constexpr (FUSE) {
-    // the block's dangling mass per column, its wavefronts added in order
-    __shared__ double s_d[kSpmmWaves][kOmega];
-    s_d[wid][lid] = f.dsum;
+    // the block's dangling mass per column: its wavefronts and groups in order
+    __shared__ double s_d[kSpmmWaves * kOmega];
+    s_d[threadIdx.x] = f.dsum;
     __syncthreads();
-    if (wid == 0 && lane_on) {
+    if (threadIdx.x < a.k) {
       double d = 0.0;
-      for (int w = 0; w < kSpmmWaves; ++w) d += s_d[w][lid];
-      double* o = a.part + ((int64_t)blockIdx.x * kOmega + a.col0 + lid) * 2;
+      for (int w = 0; w < kSpmmWaves * G; ++w) d += s_d[w * KP + threadIdx.x];
+      double* o = a.part + ((int64_t)blockIdx.x * kOmega + a.col0 + threadIdx.x) * 2;
       o[0] = d;
       o[1] = 0.0;
     }
@@ -269,36 +230,33 @@ __global__ __launch_bounds__(kSpmmWaves * 64) void spmm_kernel(SpmmArgs a) {
 
 int spmm_blocks(int64_t tile_num) { return (int)((tile_num + kSpmmWaves - 1) / kSpmmWaves); }
 
-template <typename V, int S>
-static hipError_t spmm_launch_t(const SpmmArgs& a, hipStream_t st) {
+template <typename V, int KP>
+static hipError_t spmm_launch_t(const SpmmArgs& a, int sigma, hipStream_t st) {
   const unsigned grid = (unsigned)spmm_blocks(a.tile_num);
+  const size_t lds = (size_t)kSpmmWaves * spmm_wave_lds<V>(sigma);
   if (a.Xn != nullptr)
-    hipLaunchKernelGGL((spmm_kernel<V, S, true>), dim3(grid), dim3(kSpmmWaves * 64), 0, st, a);
+    hipLaunchKernelGGL((spmm_kernel<V, KP, true>), dim3(grid), dim3(kSpmmWaves * 64), lds, st, a,
+                       sigma);
   else
-    hipLaunchKernelGGL((spmm_kernel<V, S, false>), dim3(grid), dim3(kSpmmWaves * 64), 0, st, a);
+    hipLaunchKernelGGL((spmm_kernel<V, KP, false>), dim3(grid), dim3(kSpmmWaves * 64), lds, st, a,
+                       sigma);
   return hipGetLastError();
 }
 
-typedef hipError_t (*spmm_fn)(const SpmmArgs&, hipStream_t);
-
 template <typename V>
-static spmm_fn spmm_pick(int sigma) {
-  switch (sigma) {
-#define MERBIT_MCASE(S) \
-  case S: return spmm_launch_t<V, S>;
-    MERBIT_MCASE(1) MERBIT_MCASE(2) MERBIT_MCASE(3) MERBIT_MCASE(4) MERBIT_MCASE(5)
-    MERBIT_MCASE(6) MERBIT_MCASE(7) MERBIT_MCASE(8) MERBIT_MCASE(9) MERBIT_MCASE(10)
-    MERBIT_MCASE(11) MERBIT_MCASE(12)
-#undef MERBIT_MCASE
-    default: return nullptr;
-  }
+static hipError_t spmm_pick(const SpmmArgs& a, int sigma, hipStream_t st) {
+  if (a.k <= 1) return spmm_launch_t<V, 1>(a, sigma, st);
+  if (a.k <= 2) return spmm_launch_t<V, 2>(a, sigma, st);
+  if (a.k <= 4) return spmm_launch_t<V, 4>(a, sigma, st);
+  if (a.k <= 8) return spmm_launch_t<V, 8>(a, sigma, st);
+  if (a.k <= 16) return spmm_launch_t<V, 16>(a, sigma, st);
+  return spmm_launch_t<V, 32>(a, sigma, st);
 }
 
 hipError_t launch_spmm(int dtype, int sigma, const SpmmArgs& a, hipStream_t st) {
   if (a.tile_num == 0) return hipSuccess;
-  spmm_fn f = dtype == 0 ? spmm_pick<float>(sigma) : spmm_pick<double>(sigma);
-  if (!f) return hipErrorInvalidValue;
-  return f(a, st);
+  if (sigma < 1 || sigma > kMaxSigma || a.k < 1 || a.k > kSlab) return hipErrorInvalidValue;
+  return dtype == 0 ? spmm_pick<float>(a, sigma, st) : spmm_pick<double>(a, sigma, st);
 }
 
 // Zero Y[tile_y[t], col0 .. col0 + k) for every tile t (the rows the SpMM adds onto).

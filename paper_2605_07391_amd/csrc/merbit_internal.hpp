@@ -138,6 +138,31 @@ __device__ __forceinline__ void tile_nz_rows(const uint32_t* __restrict__ lane_d
   }
 }
 
+// The same with sigma as an argument and 16-bit rows (a tile has at most 64
+// sigma < 2^16 of them).
+__device__ __forceinline__ void tile_nz_rows(const uint32_t* __restrict__ lane_desc, int lane_num,
+                                             int path_len, int sigma, int t, uint32_t tyw,
+                                             int x_se, int lid, uint16_t* wrow) {
+  if (x_se <= 0) return;
+  if (tyw & kFastBit) {
+    for (int q = lid; q < x_se; q += kOmega) wrow[q] = 0;
+    return;
+  }
+  const int j = t * kOmega + lid;
+  if (j >= lane_num) return;
+  const int bits = 32 - __builtin_clz(kOmega * sigma - 1);  // ceil(log2(64 sigma))
+  const uint32_t mask = (1u << bits) - 1u;
+  const uint32_t d = lane_desc[j];
+  int xo = (int)(d & mask);
+  int yo = (int)((d >> bits) & mask);
+  uint32_t flags = d >> (2 * bits);
+  const int steps = min(sigma, path_len - j * sigma);
+  for (int k = 0; k < steps; ++k, flags >>= 1) {
+    if (flags & 1u) ++yo;
+    else wrow[xo++] = (uint16_t)yo;
+  }
+}
+
 // Threads per block of the reduction kernels.
 constexpr int kReduceThreads = 256;
 

@@ -59,6 +59,37 @@ def test_spmm_parity(name, sigma, k, dtype):
     plan.close()
 
 
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+@pytest.mark.parametrize("k", [2, 3, 4, 7, 8, 12, 16, 20, 24, 32])
+@pytest.mark.parametrize("pad", [0, 1, 4])
+def test_spmm_group_widths(pad, k, dtype):
+    """Every group width of the SpMM's wavefront (1 to 32 lanes, one to four
+    columns per lane), with row strides that allow and that forbid wide
+    accesses: one long row over several tiles, rows of one to three nonzeros,
+    empty rows at the start, between and at the end, and a last tile of a few
+    steps."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    rng = np.random.default_rng(100 + k)
+    lens = np.concatenate([np.zeros(70, int), [2000], rng.integers(0, 4, 700), np.zeros(130, int),
+                           [1, 0, 449, 5], np.zeros(9, int)])
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    nc = 501
+    col = rng.integers(0, nc, rp[-1]).astype(np.int32)
+    vals = rng.uniform(-1, 1, rp[-1])
+    r, c, v = to_device(rp, col, vals, dtype, dev)
+    plan = pkg.Plan(r, c, v, nc, sigma=7)
+    X64 = seeded_X(nc, k, 300 + k, dtype)
+    Xw = torch.full((nc, k + pad), float("nan"), dtype=dtype, device=dev)
+    Xw[:, :k] = torch.from_numpy(X64).to(dtype).to(dev)
+    Yw = torch.full((len(rp) - 1, k + pad), float("nan"), dtype=dtype, device=dev)
+    plan.spmm(Xw[:, :k], out=Yw[:, :k])
+    torch.cuda.synchronize()
+    check_spmm(Yw[:, :k], rp, col, host_values(vals, dtype), X64, dtype, f"k {k} pad {pad}")
+    assert pad == 0 or torch.isnan(Yw[:, k:]).all()
+    plan.close()
+
+
 @pytest.mark.parametrize("k", [64, 13])
 @pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
 def test_spmm_x_beyond_2gib(dtype, k):
