@@ -6,9 +6,10 @@
 // SpMM (one wavefront per tile; the driver runs one launch per slab of 32
 // columns).  The tile's merge-path segment (Sec. 4.1) fixes its nonzeros
 // [x_ws, x_we) and rows [y_ws, y_we]; every nonzero is a row operation
-// Y[row, :] += v * X[col, :].  The wavefront is cut into groups of KP lanes,
-// KP the power of two that holds the slab's columns, and each group takes an
-// equal run of the tile's nonzeros, its lanes the columns:
+// Y[row, :] += v * X[col, :].  A lane carries W columns (one 16-byte access
+// where the operands' alignment allows it); the wavefront is cut into groups
+// of KP lanes, KP the power of two that holds the slab's columns, and each
+// group takes an equal run of the tile's nonzeros:
 //   1. the tile's values, X row offsets and rows (decoded from the lane
 //      descriptors, Sec. 4.1.1) go to LDS;
 //   2. each group walks its run, kSpmmUnroll X rows in flight before the first
@@ -20,56 +21,76 @@
 // (shared with neighbouring tiles) are added atomically to Y, which is zero
 // there before the launch.
 //
-// What bounds it: with 17 to 32 columns on large graphs the X row reads that
-// miss L2 (R-MAT 20, 32 columns, FP32: 2 GB of them in 284 us); below that the
-// instructions per nonzero, which the groups divide by 64 / KP.  A wavefront
-// that walks one nonzero at a time, its idle lanes repeating the last column,
-// takes as long for 1 column as for 32: R-MAT 18 FP32, 1 / 5 / 16 / 32
-// columns 102 / 102 / 102 / 103 us, now 40 / 51 / 64 / 95; FP64 153 / 153 /
-// 154 / 158, now 45 / 56 / 63 / 106; Chung-Lu 100,003 FP64, 5 columns 49.0,
-// now 21.0.  sigma is an argument, not a template parameter: only the staging
+// What bounds it: on large graphs the X row reads that miss L2 (R-MAT 20, 32
+// columns, FP32: 2 GB of them in 238 us); otherwise the instructions per
+// nonzero, which the groups divide by 64 / KP.  A wavefront that walks one
+// nonzero at a time, its idle lanes repeating the last column, takes as long
+// for 1 column as for 32.  R-MAT 18, 2 / 8 / 16 / 32 columns, one nonzero at a
+// time, then groups of one column per lane, then several columns per lane:
+// FP32 102 / 103 / 103 / 103, 44 / 51 / 64 / 96, 42 / 46 / 48 / 55 us; FP64
+// 153 / 154 / 154 / 160, 45 / 51 / 64 / 107, 44 / 50 / 51 / 103 us.  sigma is an argument, not a template parameter: only the staging
 // loops depend on it.
 #include "merbit_internal.hpp"
 
 namespace merbit {
 
 constexpr int kSpmmWaves = 4;
-// X rows in flight per group before the first is used (R-MAT 18 FP32, 32
-// columns: 129 / 105 / 95 us at 4 / 8 / 16)
+// X rows in flight per group before the first is used: 16 loads of one column
+// per lane (R-MAT 18 FP32, 32 columns: 129 / 105 / 95 us at 4 / 8 / 16), 8 of
+// several (61 / 55 / 53 us; FP64 100 / 103 / 105 us, 8 columns on Chung-Lu
+// 700,001 88 / 86 / 99 us)
 constexpr int kSpmmUnroll = 16;
+constexpr int kSpmmUnrollWide = 8;
 // word 3 of a raw (unformatted, stride 0) buffer resource on gfx950
 constexpr int kSpmmBufferWord3 = 0x00020000;
 
+// W consecutive columns of a row
+template <typename V, int W>
+struct Cols {
+  typedef V type __attribute__((ext_vector_type(W)));
+};
+
 // Per-lane state of a fused personalised-PageRank step (SpmmArgs::Xn).
-template <typename V>
+template <typename V, int W>
 struct PprRow {
   V* Xn;
   int64_t ld;
   V a;                 // alpha
-  V tele;              // alpha delta_j + 1 - alpha, added at the column's source row
-  int sj;              // the column's source row (-1: lane past the slab)
+  V tele[W];           // alpha delta_j + 1 - alpha, added at the column's source row
+  int sj[W];           // the column's source row (-1: lane past the slab)
   int w0;              // dmask word of the tile's first row
   const uint32_t* dm;  // the tile's dmask words (LDS)
-  double dsum;         // dangling mass of the rows this lane finished
+  double dsum[W];      // dangling mass of the rows this lane finished
 };
 
-// Column j of row row_abs (rel within the tile) is complete.  The tile's
-// first and last rows are shared with neighbouring tiles and are added to Y;
-// the others are stored, or with FUSE finished as the next iterate.
-template <typename V, bool FUSE>
+// Columns j .. j + W - 1 of row y_ws + rel are complete.  The tile's first and
+// last rows are shared with neighbouring tiles and are added to Y; the others
+// are stored, or with FUSE finished as the next iterate.
+template <typename V, int W, bool FUSE>
 __device__ __forceinline__ void spmm_row(const SpmmArgs& a, int j, int y_ws, int rel,
-                                         int last_rel, V acc, PprRow<V>& f) {
+                                         int last_rel, typename Cols<V, W>::type acc,
+                                         PprRow<V, W>& f) {
+  typedef typename Cols<V, W>::type VW;
   const int row = y_ws + rel;
   V* y = static_cast<V*>(a.Y) + (int64_t)row * a.ldy + j;
   if (rel == 0 || rel == last_rel) {
-    if (row < a.n_rows) global_add(y, acc);
+    if (row < a.n_rows)
+#pragma unroll
+      for (int c = 0; c < W; ++c) global_add(y + c, acc[c]);
   } else if constexpr (FUSE) {
-    V xn = f.a * acc;
-    if (row == f.sj) xn += f.tele;
-    __builtin_nontemporal_store(xn, f.Xn + (int64_t)row * f.ld + j);
-    if ((f.dm[(row >> 5) - f.w0] >> (row & 31)) & 1u) f.dsum += (double)xn;
+    VW xn;
+    const bool dangling = (f.dm[(row >> 5) - f.w0] >> (row & 31)) & 1u;
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+      V v = f.a * acc[c];
+      if (row == f.sj[c]) v += f.tele[c];
+      xn[c] = v;
+      if (dangling) f.dsum[c] += (double)v;
+    }
+    __builtin_nontemporal_store(xn, reinterpret_cast<VW*>(f.Xn + (int64_t)row * f.ld + j));
   } else {
-    __builtin_nontemporal_store(acc, y);  // written once, not read here again
+    // written once, not read here again
+    __builtin_nontemporal_store(acc, reinterpret_cast<VW*>(y));
   }
 }
 
@@ -80,24 +101,29 @@ static __host__ __device__ constexpr int spmm_wave_lds(int sigma) {
   return kOmega * sigma * ((int)sizeof(V) + 4 + 2 + 1) + kOmega * 4;
 }
 
-template <typename V, int KP, bool FUSE>
+// KP lanes per group, W columns per lane: KP W >= a.k, a.k a multiple of W.
+template <typename V, int KP, int W, bool FUSE>
 __global__ __launch_bounds__(kSpmmWaves * 64) void spmm_kernel(SpmmArgs a, int sigma) {
+  typedef typename Cols<V, W>::type VW;
   constexpr int G = kOmega / KP;  // groups of KP lanes
-  constexpr int U = kSpmmUnroll;
+  constexpr int U = W == 1 ? kSpmmUnroll : kSpmmUnrollWide;
   extern __shared__ __align__(16) unsigned char s_dyn[];
   const int lid = threadIdx.x & (kOmega - 1);
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kOmega);
-  const int g = lid / KP, j = lid % KP;
+  const int g = lid / KP, j = lid % KP * W;
   const int t = blockIdx.x * kSpmmWaves + wid;
   const bool on = j < a.k;
-  PprRow<V> f{};
+  PprRow<V, W> f{};
   if constexpr (FUSE) {
     f.Xn = static_cast<V*>(a.Xn);
     f.ld = a.ldx;
     f.a = (V)a.alpha;
-    f.sj = on ? a.src[j] : -1;
-    f.tele = on ? (V)(a.alpha * a.sums_in[2 * j] + 1.0 - a.alpha) : V(0);
-    f.dsum = 0.0;
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+      f.sj[c] = on ? a.src[j + c] : -1;
+      f.tele[c] = on ? (V)(a.alpha * a.sums_in[2 * (j + c)] + 1.0 - a.alpha) : V(0);
+      f.dsum[c] = 0.0;
+    }
   }
   if (t < a.tile_num) {
     const int T = kOmega * sigma;
@@ -145,16 +171,17 @@ __global__ __launch_bounds__(kSpmmWaves * 64) void spmm_kernel(SpmmArgs a, int s
     const int cnt = min(max(x_se - q0, 0), L);
     int cur0 = 0, cur = 0;
     bool has = false;
-    V acc = V(0), first = V(0);
+    VW acc = VW(0), first = VW(0);
     if (cnt > 0) cur0 = cur = s_row[q0 > 0 ? q0 - 1 : 0];
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
         (void*)X, (short)0,
         buf ? (int)(((a.x_rows - 1) * a.ldx + a.k) * (int64_t)sizeof(V)) : 0, kSpmmBufferWord3);
-    const int jx = min(j, a.k - 1);  // lanes past k read the row's last column again
+    const int jx = min(j, a.k - W);  // lanes past k read the row's last columns again
     auto walk = [&](auto load) {
       for (int i = 0; i < cnt; i += U) {
         uint32_t off[U];
-        V v[U], x[U];
+        V v[U];
+        VW x[U];
         uint16_t r[U];
         const int q = q0 + i;  // a multiple of U: aligned vector reads
 #pragma unroll
@@ -170,57 +197,68 @@ __global__ __launch_bounds__(kSpmmWaves * 64) void spmm_kernel(SpmmArgs a, int s
           if (i + u < cnt) {
             if ((int)r[u] != cur) {
               if (!has) first = acc;
-              else if (on) spmm_row<V, FUSE>(a, j, y_ws, cur, last_rel, acc, f);
+              else if (on) spmm_row<V, W, FUSE>(a, j, y_ws, cur, last_rel, acc, f);
               has = true;
               cur = r[u];
-              acc = V(0);
+              acc = VW(0);
             }
-            acc += v[u] * x[u];
+#pragma unroll
+            for (int c = 0; c < W; ++c) acc[c] += v[u] * x[u][c];
           }
         }
       }
     };
     if (buf) {
-      walk([&](uint32_t off) -> V {
-        if constexpr (sizeof(V) == 4)
-          return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(rx, off + jx * 4, 0, 0));
+      walk([&](uint32_t off) -> VW {
+        const int at = (int)off + jx * (int)sizeof(V);
+        if constexpr (sizeof(VW) == 4)
+          return __builtin_bit_cast(VW, __builtin_amdgcn_raw_buffer_load_b32(rx, at, 0, 0));
+        else if constexpr (sizeof(VW) == 8)
+          return __builtin_bit_cast(VW, __builtin_amdgcn_raw_buffer_load_b64(rx, at, 0, 0));
         else
-          return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rx, off + jx * 8, 0, 0));
+          return __builtin_bit_cast(VW, __builtin_amdgcn_raw_buffer_load_b128(rx, at, 0, 0));
       });
     } else {
-      walk([&](uint32_t c) -> V { return X[(int64_t)c * a.ldx + jx]; });
+      walk([&](uint32_t c) -> VW {
+        return *reinterpret_cast<const VW*>(X + (int64_t)c * a.ldx + jx);
+      });
     }
     // 3. the groups' carries: a segmented scan over the groups of a column
-    V sum = acc;
+    VW sum = acc;
     int head = has;
 #pragma unroll
     for (int d = KP; d < kOmega; d <<= 1) {
-      const V ts = __shfl_up(sum, d, kOmega);
+      VW ts;
+#pragma unroll
+      for (int c = 0; c < W; ++c) ts[c] = __shfl_up(sum[c], d, kOmega);
       const int th = __shfl_up(head, d, kOmega);
       if (lid >= d) {
         if (!head) sum += ts;
         head |= th;
       }
     }
-    const V below = __shfl_up(sum, KP, kOmega);
-    if (has && on)
-      spmm_row<V, FUSE>(a, j, y_ws, cur0, last_rel, first + (g > 0 ? below : V(0)), f);
+    VW carry;
+#pragma unroll
+    for (int c = 0; c < W; ++c) carry[c] = __shfl_up(sum[c], KP, kOmega);
+    if (g == 0) carry = VW(0);
+    if (has && on) spmm_row<V, W, FUSE>(a, j, y_ws, cur0, last_rel, first + carry, f);
     if (x_se > 0 && g == G - 1 && on)
-      spmm_row<V, FUSE>(a, j, y_ws, s_row[x_se - 1], last_rel, sum, f);
+      spmm_row<V, W, FUSE>(a, j, y_ws, s_row[x_se - 1], last_rel, sum, f);
     // 4. the empty rows strictly inside the tile
     for (int e = 1 + g; e < last_rel; e += G)
-      if (!s_has[e] && on) spmm_row<V, FUSE>(a, j, y_ws, e, last_rel, V(0), f);
+      if (!s_has[e] && on) spmm_row<V, W, FUSE>(a, j, y_ws, e, last_rel, VW(0), f);
     if (a.Z != nullptr && g == 0 && on)
-      static_cast<V*>(a.Z)[(int64_t)y_ws * a.ldz + j] = V(0);
+      *reinterpret_cast<VW*>(static_cast<V*>(a.Z) + (int64_t)y_ws * a.ldz + j) = VW(0);
   }
   if constexpr (FUSE) {
     // the block's dangling mass per column: its wavefronts and groups in order
-    __shared__ double s_d[kSpmmWaves * kOmega];
-    s_d[threadIdx.x] = f.dsum;
+    __shared__ double s_d[kSpmmWaves * kOmega * W];
+#pragma unroll
+    for (int c = 0; c < W; ++c) s_d[threadIdx.x * W + c] = f.dsum[c];
     __syncthreads();
     if (threadIdx.x < a.k) {
       double d = 0.0;
-      for (int w = 0; w < kSpmmWaves * G; ++w) d += s_d[w * KP + threadIdx.x];
+      for (int w = 0; w < kSpmmWaves * G; ++w) d += s_d[w * KP * W + threadIdx.x];
       double* o = a.part + ((int64_t)blockIdx.x * kOmega + a.col0 + threadIdx.x) * 2;
       o[0] = d;
       o[1] = 0.0;
@@ -230,33 +268,53 @@ __global__ __launch_bounds__(kSpmmWaves * 64) void spmm_kernel(SpmmArgs a, int s
 
 int spmm_blocks(int64_t tile_num) { return (int)((tile_num + kSpmmWaves - 1) / kSpmmWaves); }
 
-template <typename V, int KP>
+template <typename V, int KP, int W>
 static hipError_t spmm_launch_t(const SpmmArgs& a, int sigma, hipStream_t st) {
   const unsigned grid = (unsigned)spmm_blocks(a.tile_num);
   const size_t lds = (size_t)kSpmmWaves * spmm_wave_lds<V>(sigma);
   if (a.Xn != nullptr)
-    hipLaunchKernelGGL((spmm_kernel<V, KP, true>), dim3(grid), dim3(kSpmmWaves * 64), lds, st, a,
-                       sigma);
+    hipLaunchKernelGGL((spmm_kernel<V, KP, W, true>), dim3(grid), dim3(kSpmmWaves * 64), lds, st,
+                       a, sigma);
   else
-    hipLaunchKernelGGL((spmm_kernel<V, KP, false>), dim3(grid), dim3(kSpmmWaves * 64), lds, st, a,
-                       sigma);
+    hipLaunchKernelGGL((spmm_kernel<V, KP, W, false>), dim3(grid), dim3(kSpmmWaves * 64), lds, st,
+                       a, sigma);
   return hipGetLastError();
 }
 
+// Columns per lane: as many as one 16-byte access holds, if every row of every
+// operand allows it, so that a group needs fewer lanes.
 template <typename V>
+static bool spmm_wide(const SpmmArgs& a, int w) {
+  const uintptr_t mask = (uintptr_t)w * sizeof(V) - 1;
+  auto at = [&](const void* p, int64_t ld) {
+    return p == nullptr || ((reinterpret_cast<uintptr_t>(p) & mask) == 0 && ld % w == 0);
+  };
+  return a.k % w == 0 && at(a.X, a.ldx) && at(a.Y, a.ldy) && at(a.Z, a.ldz) && at(a.Xn, a.ldx);
+}
+
+template <typename V, int W>
 static hipError_t spmm_pick(const SpmmArgs& a, int sigma, hipStream_t st) {
-  if (a.k <= 1) return spmm_launch_t<V, 1>(a, sigma, st);
-  if (a.k <= 2) return spmm_launch_t<V, 2>(a, sigma, st);
-  if (a.k <= 4) return spmm_launch_t<V, 4>(a, sigma, st);
-  if (a.k <= 8) return spmm_launch_t<V, 8>(a, sigma, st);
-  if (a.k <= 16) return spmm_launch_t<V, 16>(a, sigma, st);
-  return spmm_launch_t<V, 32>(a, sigma, st);
+  const int lanes = a.k / W;
+  if (lanes <= 1) return spmm_launch_t<V, 1, W>(a, sigma, st);
+  if (lanes <= 2) return spmm_launch_t<V, 2, W>(a, sigma, st);
+  if (lanes <= 4) return spmm_launch_t<V, 4, W>(a, sigma, st);
+  if (lanes <= 8) return spmm_launch_t<V, 8, W>(a, sigma, st);
+  if constexpr (W <= 2)
+    if (lanes <= 16) return spmm_launch_t<V, 16, W>(a, sigma, st);
+  if constexpr (W == 1) return spmm_launch_t<V, 32, W>(a, sigma, st);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_spmm(int dtype, int sigma, const SpmmArgs& a, hipStream_t st) {
   if (a.tile_num == 0) return hipSuccess;
   if (sigma < 1 || sigma > kMaxSigma || a.k < 1 || a.k > kSlab) return hipErrorInvalidValue;
-  return dtype == 0 ? spmm_pick<float>(a, sigma, st) : spmm_pick<double>(a, sigma, st);
+  if (dtype == 0) {
+    if (spmm_wide<float>(a, 4)) return spmm_pick<float, 4>(a, sigma, st);
+    if (spmm_wide<float>(a, 2)) return spmm_pick<float, 2>(a, sigma, st);
+    return spmm_pick<float, 1>(a, sigma, st);
+  }
+  if (spmm_wide<double>(a, 2)) return spmm_pick<double, 2>(a, sigma, st);
+  return spmm_pick<double, 1>(a, sigma, st);
 }
 
 // Zero Y[tile_y[t], col0 .. col0 + k) for every tile t (the rows the SpMM adds onto).
