@@ -383,11 +383,12 @@ hipError_t launch_tile_rows(int dtype, int sigma, bool sddmm, const TileRowsArgs
                             hipStream_t st);
 // CSR of A^T from the rows and columns of A's nonzeros (stable by row):
 // rowT [n_cols + 1], colT [m], perm [m] (A position of each A^T nonzero).
-// temp: transpose_temp_bytes(m, end_bit) bytes; columns are < 2^end_bit.
+// temp: transpose_temp_bytes(m, end_bit) bytes; columns are < 2^end_bit.  The
+// rows of A's nonzeros are first written to transpose_rows(): temp or colT.
 size_t transpose_temp_bytes(int64_t m, int end_bit);
-hipError_t launch_transpose(const int32_t* col, const int32_t* rows, int64_t m, int64_t n_cols,
-                            int end_bit, void* temp, int32_t* rowT, int32_t* colT,
-                            int32_t* perm, hipStream_t st);
+int32_t* transpose_rows(int64_t m, int end_bit, void* temp, int32_t* colT);
+hipError_t launch_transpose(const int32_t* col, int64_t m, int64_t n_cols, int end_bit, void* temp,
+                            int32_t* rowT, int32_t* colT, int32_t* perm, hipStream_t st);
 hipError_t launch_gather_values(int dtype, const int32_t* perm, const void* src, const void* src2,
                                 void* dst, int64_t m, hipStream_t st);
 hipError_t launch_column_scale(int dtype, const int32_t* col, const void* a, const void* t,
@@ -417,8 +418,9 @@ hipError_t launch_bicg(int dtype, const BicgArgs& a, int stage, hipStream_t st);
 
 // Scans of int32 arrays (in == out allowed) and one stable radix-sort pass
 // of (key, value) pairs by the digit (key >> shift) & (2^bits - 1), bits in
-// 1..8 (val_in == nullptr: the values are the positions 0 .. n - 1).  temp:
-// scan_temp_bytes(n) / radix_temp_bytes(n, bits) bytes of device memory.
+// 1..8 (val_in == nullptr: the values are the positions 0 .. n - 1; val2_in:
+// a second value per key).  temp: scan_temp_bytes(n) / radix_temp_bytes(n,
+// bits) bytes of device memory.
 enum ScanKind { kScanExclusiveSum = 0, kScanInclusiveSum = 1, kScanInclusiveMax = 2 };
 size_t scan_temp_bytes(int64_t n);
 hipError_t launch_scan_i32(const int32_t* in, int32_t* out, int64_t n, ScanKind kind,
@@ -426,7 +428,8 @@ hipError_t launch_scan_i32(const int32_t* in, int32_t* out, int64_t n, ScanKind 
 size_t radix_temp_bytes(int64_t n, int bits);
 hipError_t launch_radix_pass(const uint32_t* key_in, const int32_t* val_in, uint32_t* key_out,
                              int32_t* val_out, int64_t n, int shift, int bits, void* temp,
-                             hipStream_t st);
+                             hipStream_t st, const int32_t* val2_in = nullptr,
+                             int32_t* val2_out = nullptr);
 
 // Column stripes (a matrix stacked by column stripe, rows = the non-empty
 // (stripe, row) pairs) and the per-row sum of the stripes' results.

@@ -5,17 +5,26 @@
 // its chunk, one block scans the chunk totals, each block scans its chunk
 // from its total's prefix.  Sum and max, inclusive or exclusive, int32.
 //
-// Radix pass: a stable counting sort of (key, value) pairs by the digit
-// (key >> shift) & (2^bits - 1), bits <= 8.  Each wavefront owns a segment of
-// kSortSeg consecutive pairs.  A first launch counts the digits of every
-// segment (the lanes that hold equal digits find each other with one ballot
-// per digit bit, and the highest of them adds their number to the
-// wavefront's LDS counter); the counts, stored digit-major, are scanned; a
-// second launch walks the segment again in the same order and writes each
-// pair at its digit's running position.  Digit-major order of the counts
-// keeps equal digits in segment order, and the walk keeps them in order
-// inside a segment, so the pass is stable.  LSD passes over successive digit
-// fields sort by the whole key.
+// Radix pass: a stable counting sort of (key, value[, value]) records by the
+// digit (key >> shift) & (2^bits - 1), bits <= 8.  A block owns kSortBlock
+// consecutive records, each of its wavefronts a run of them.  A first launch
+// counts the digits of every block; the counts, stored digit-major, are
+// scanned; a second launch ranks the block's records by digit (the lanes that
+// hold equal digits find each other with one ballot per digit bit, and the
+// highest of them advances the wavefront's LDS counter), puts them in digit
+// order in LDS and writes them from there, so that consecutive lanes write
+// consecutive records of a digit's run.  Digit-major order of the counts keeps
+// equal digits in block order, and ranks keep them in order inside a block, so
+// the pass is stable.  LSD passes over successive digit fields sort by the
+// whole key.
+//
+// What bounds it: the scattered runs (16 records of a digit per block at 8
+// bits) against 12 or 20 bytes read and written per record.  Records written
+// straight from the lanes (64 places per store) took 255 us per pass of 15.7M
+// (column, position) pairs of R-MAT 20; reordered, with a third word per
+// record, 111 us (145 us with an LDS array per word: three blocks per CU
+// instead of five).  The count takes 19 us (49 us with a ballot per digit
+// bit instead of LDS atomics).
 #include <limits.h>
 
 #include "merbit_internal.hpp"
@@ -186,9 +195,12 @@ hipError_t launch_scan_i32(const int32_t* in, int32_t* out, int64_t n, ScanKind 
 // ------------------------------------------------------------ radix pass --
 
 constexpr int kSortWaves = 4;
-constexpr int kSortItems = 32;
-constexpr int kSortSeg = kOmega * kSortItems;
+constexpr int kSortThreads = kSortWaves * kOmega;
+constexpr int kSortItems = 16;  // records per thread (8: level; 32: 15 % slower)
+constexpr int kSortRun = kOmega * kSortItems;
+constexpr int kSortBlock = kSortWaves * kSortRun;
 constexpr int kSortMaxDigits = 256;
+static_assert(kSortThreads == kSortMaxDigits, "one thread per digit");
 
 // Lanes of the wavefront whose `valid` digit equals this lane's.
 __device__ __forceinline__ unsigned long long digit_peers(uint32_t d, bool valid, int bits) {
@@ -201,91 +213,156 @@ __device__ __forceinline__ unsigned long long digit_peers(uint32_t d, bool valid
   return m;
 }
 
-__global__ __launch_bounds__(kSortWaves * kOmega) void radix_count_kernel(
-    const uint32_t* __restrict__ key, int64_t n, int shift, int bits, int64_t nseg,
+// counts[d * nblk + b] = records of digit d in block b
+__global__ __launch_bounds__(kSortThreads) void radix_count_kernel(
+    const uint32_t* __restrict__ key, int64_t n, int shift, int bits, int64_t nblk,
     int32_t* __restrict__ counts) {
+  // one set of counters per wavefront: equal digits of a wavefront meet anyway
   __shared__ int32_t s_cnt[kSortWaves][kSortMaxDigits];
-  const int lid = threadIdx.x & (kOmega - 1);
-  const int wid = threadIdx.x / kOmega;
-  const int64_t seg = (int64_t)blockIdx.x * kSortWaves + wid;
-  if (seg >= nseg) return;  // no block-wide barrier below
-  const int nd = 1 << bits;
-  const uint32_t dmask = (uint32_t)nd - 1u;
-  int32_t* cnt = s_cnt[wid];
-  for (int d = lid; d < nd; d += kOmega) cnt[d] = 0;
-  wave_lds_sync();
-  const int64_t base = seg * kSortSeg;
+  const int tid = threadIdx.x, wid = tid / kOmega;
+  const uint32_t dmask = (1u << bits) - 1u;
+  for (int w = 0; w < kSortWaves; ++w) s_cnt[w][tid] = 0;
+  const int64_t base = (int64_t)blockIdx.x * kSortBlock;
+  uint32_t k[kSortItems];
+#pragma unroll
   for (int it = 0; it < kSortItems; ++it) {
-    const int64_t i = base + (int64_t)it * kOmega + lid;
-    const bool valid = i < n;
-    const uint32_t d = valid ? (key[i] >> shift) & dmask : 0u;
-    const unsigned long long peers = digit_peers(d, valid, bits);
-    // the highest lane of each group of equal digits adds the group's size
-    if (valid && 63 - __builtin_clzll(peers) == lid) cnt[d] += __popcll(peers);
-    wave_lds_sync();
+    const int64_t i = base + it * kSortThreads + tid;
+    k[it] = i < n ? key[i] : 0u;
   }
-  for (int d = lid; d < nd; d += kOmega) counts[(int64_t)d * nseg + seg] = cnt[d];
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < kSortItems; ++it)
+    if (base + it * kSortThreads + tid < n) atomicAdd(&s_cnt[wid][(k[it] >> shift) & dmask], 1);
+  __syncthreads();
+  if (tid <= (int)dmask) {
+    int32_t c = 0;
+    for (int w = 0; w < kSortWaves; ++w) c += s_cnt[w][tid];
+    counts[(int64_t)tid * nblk + blockIdx.x] = c;
+  }
 }
 
-__global__ __launch_bounds__(kSortWaves * kOmega) void radix_scatter_kernel(
+template <bool TWO>
+__global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
     const uint32_t* __restrict__ key_in, const int32_t* __restrict__ val_in,
-    uint32_t* __restrict__ key_out, int32_t* __restrict__ val_out, int64_t n, int shift,
-    int bits, int64_t nseg, const int32_t* __restrict__ offsets) {
-  __shared__ int32_t s_pos[kSortWaves][kSortMaxDigits];
-  const int lid = threadIdx.x & (kOmega - 1);
-  const int wid = threadIdx.x / kOmega;
-  const int64_t seg = (int64_t)blockIdx.x * kSortWaves + wid;
-  if (seg >= nseg) return;
-  const int nd = 1 << bits;
-  const uint32_t dmask = (uint32_t)nd - 1u;
-  int32_t* pos = s_pos[wid];
-  for (int d = lid; d < nd; d += kOmega) pos[d] = offsets[(int64_t)d * nseg + seg];
-  wave_lds_sync();
-  const unsigned long long below = (1ull << lid) - 1ull;
-  const int64_t base = seg * kSortSeg;
+    const int32_t* __restrict__ val2_in, uint32_t* __restrict__ key_out,
+    int32_t* __restrict__ val_out, int32_t* __restrict__ val2_out, int64_t n, int shift, int bits,
+    int64_t nblk, const int32_t* __restrict__ offsets) {
+  __shared__ uint32_t s_rec[kSortBlock];  // the keys, then each value, in digit order
+  __shared__ int32_t s_cnt[kSortWaves][kSortMaxDigits];
+  __shared__ int32_t s_goff[kSortMaxDigits];
+  __shared__ int32_t s_wave[kSortWaves];
+  const int tid = threadIdx.x, lid = tid & (kOmega - 1), wid = tid / kOmega;
+  const uint32_t dmask = (1u << bits) - 1u;
+  for (int w = 0; w < kSortWaves; ++w) s_cnt[w][tid] = 0;
+  const int64_t base = (int64_t)blockIdx.x * kSortBlock;
+  const int n_blk = (int)(n - base < kSortBlock ? n - base : kSortBlock);
+  const int first = wid * kSortRun + lid;  // this thread's records: first + 64 it
+  uint32_t k[kSortItems];
+  int32_t v[kSortItems], v2[kSortItems];  // v2 only with TWO
+#pragma unroll
   for (int it = 0; it < kSortItems; ++it) {
-    const int64_t i = base + (int64_t)it * kOmega + lid;
-    const bool valid = i < n;
-    const uint32_t k = valid ? key_in[i] : 0u;
-    const uint32_t d = (k >> shift) & dmask;
+    const int q = first + it * kOmega;
+    k[it] = q < n_blk ? key_in[base + q] : 0u;
+  }
+#pragma unroll
+  for (int it = 0; it < kSortItems; ++it) {
+    const int q = first + it * kOmega;
+    v[it] = val_in == nullptr ? (int32_t)(base + q) : (q < n_blk ? val_in[base + q] : 0);
+    if constexpr (TWO) v2[it] = q < n_blk ? val2_in[base + q] : 0;
+  }
+  __syncthreads();
+  // rank among the wavefront's records of the same digit
+  const unsigned long long below = (1ull << lid) - 1ull;
+  int32_t* cnt = s_cnt[wid];
+  int rank[kSortItems];
+#pragma unroll
+  for (int it = 0; it < kSortItems; ++it) {
+    const bool valid = first + it * kOmega < n_blk;
+    const uint32_t d = (k[it] >> shift) & dmask;
     const unsigned long long peers = digit_peers(d, valid, bits);
-    const int32_t at = valid ? pos[d] + __popcll(peers & below) : 0;
-    wave_lds_sync();  // every lane has read its digit's position
-    if (valid) {
-      key_out[at] = k;
-      val_out[at] = val_in ? val_in[i] : (int32_t)i;
-      if (63 - __builtin_clzll(peers) == lid) pos[d] = at + 1;
-    }
+    const int32_t before = cnt[d];
+    rank[it] = before + __popcll(peers & below);
+    wave_lds_sync();  // every lane has read its digit's count
+    if (valid && 63 - __builtin_clzll(peers) == lid) cnt[d] = before + __popcll(peers);
     wave_lds_sync();
   }
+  __syncthreads();
+  // thread d: where digit d begins in the block, and each wavefront's part
+  int32_t c = 0;
+#pragma unroll
+  for (int w = 0; w < kSortWaves; ++w) {
+    const int32_t own = s_cnt[w][tid];
+    s_cnt[w][tid] = c;
+    c += own;
+  }
+  int32_t total;
+  const int32_t start = block_inclusive_scan<ScanSum, kSortThreads>(c, s_wave, &total) - c;
+#pragma unroll
+  for (int w = 0; w < kSortWaves; ++w) s_cnt[w][tid] += start;
+  if (tid <= (int)dmask) s_goff[tid] = offsets[(int64_t)tid * nblk + blockIdx.x] - start;
+  __syncthreads();
+  // rank becomes the record's place in the block's digit order
+#pragma unroll
+  for (int it = 0; it < kSortItems; ++it) {
+    rank[it] += cnt[(k[it] >> shift) & dmask];
+    if (first + it * kOmega < n_blk) s_rec[rank[it]] = k[it];
+  }
+  __syncthreads();
+  int32_t to[kSortItems];  // where the block's record tid + 256 it goes
+#pragma unroll
+  for (int it = 0; it < kSortItems; ++it) {
+    const int q = tid + it * kSortThreads;
+    if (q < n_blk) {
+      const uint32_t key = s_rec[q];
+      to[it] = s_goff[(key >> shift) & dmask] + q;
+      key_out[to[it]] = key;
+    }
+  }
+  auto put = [&](const int32_t (&x)[kSortItems], int32_t* __restrict__ out) {
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it)
+      if (first + it * kOmega < n_blk) s_rec[rank[it]] = (uint32_t)x[it];
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it) {
+      const int q = tid + it * kSortThreads;
+      if (q < n_blk) out[to[it]] = (int32_t)s_rec[q];
+    }
+  };
+  put(v, val_out);
+  if constexpr (TWO) put(v2, val2_out);
 }
 
-static int64_t sort_segments(int64_t n) { return (n + kSortSeg - 1) / kSortSeg; }
+static int64_t sort_blocks(int64_t n) { return (n + kSortBlock - 1) / kSortBlock; }
 
 size_t radix_temp_bytes(int64_t n, int bits) {
-  const int64_t counts = sort_segments(n) * ((int64_t)1 << bits);
+  const int64_t counts = sort_blocks(n) * ((int64_t)1 << bits);
   return sizeof(int32_t) * (size_t)(counts > 0 ? counts : 1) + scan_temp_bytes(counts) + 256;
 }
 
 hipError_t launch_radix_pass(const uint32_t* key_in, const int32_t* val_in, uint32_t* key_out,
                              int32_t* val_out, int64_t n, int shift, int bits, void* temp,
-                             hipStream_t st) {
+                             hipStream_t st, const int32_t* val2_in, int32_t* val2_out) {
   if (n <= 0) return hipSuccess;
   if (bits < 1 || bits > 8) return hipErrorInvalidValue;
-  const int64_t nseg = sort_segments(n);
-  const int64_t nc = nseg * ((int64_t)1 << bits);
+  const int64_t nblk = sort_blocks(n);
+  const int64_t nc = nblk * ((int64_t)1 << bits);
   int32_t* counts = static_cast<int32_t*>(temp);
   int32_t* part = reinterpret_cast<int32_t*>(
       static_cast<unsigned char*>(temp) + ((sizeof(int32_t) * (size_t)nc + 255) & ~(size_t)255));
-  const unsigned grid = (unsigned)((nseg + kSortWaves - 1) / kSortWaves);
-  hipLaunchKernelGGL(radix_count_kernel, dim3(grid), dim3(kSortWaves * kOmega), 0, st, key_in, n,
-                     shift, bits, nseg, counts);
+  const dim3 grid((unsigned)nblk), block(kSortThreads);
+  hipLaunchKernelGGL(radix_count_kernel, grid, block, 0, st, key_in, n, shift, bits, nblk, counts);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = launch_scan_i32(counts, counts, nc, kScanExclusiveSum, part, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(radix_scatter_kernel, dim3(grid), dim3(kSortWaves * kOmega), 0, st, key_in,
-                     val_in, key_out, val_out, n, shift, bits, nseg, counts);
+  if (val2_in != nullptr)
+    hipLaunchKernelGGL((radix_scatter_kernel<true>), grid, block, 0, st, key_in, val_in, val2_in,
+                       key_out, val_out, val2_out, n, shift, bits, nblk, counts);
+  else
+    hipLaunchKernelGGL((radix_scatter_kernel<false>), grid, block, 0, st, key_in, val_in, val2_in,
+                       key_out, val_out, val2_out, n, shift, bits, nblk, counts);
   return hipGetLastError();
 }
 
