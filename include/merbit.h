@@ -431,7 +431,10 @@ int merbit_tune(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t* row_
 int merbit_profile_enable(merbit_plan* plan, int enable);
 int merbit_profile_read(merbit_plan* plan, int64_t* launches, double* total_ms);
 
-/* Release the plan and everything it owns (waits for its pending work). */
+/* Release the plan and everything it owns (waits for its pending work).  The
+ * library keeps up to 512 MiB of freed device memory for the plans and
+ * temporaries of later calls; it returns all of it to the device when an
+ * allocation fails, and blocks that go unused for long or exceed the bound. */
 void merbit_plan_destroy(merbit_plan* plan);
 
 /* Message of the last failed call on this thread ("" if none). */

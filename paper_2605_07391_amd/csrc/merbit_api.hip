@@ -48,7 +48,12 @@ static void drop_graphs(merbit_plan* p) {
 
 void plan_free_all(merbit_plan* p) {
   if (!p) return;
+  // the plan's blocks may go to any stream next: wait for its device
+  int dev = 0;
+  const bool other = hipGetDevice(&dev) == hipSuccess && dev != p->device;
+  if (other) (void)hipSetDevice(p->device);
   (void)hipDeviceSynchronize();
+  if (other) (void)hipSetDevice(dev);
   drop_graphs(p);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   void* bufs[] = {p->tile_x, p->tile_y, p->lane_desc, p->lane_desc64, p->scratch, p->dmask,
@@ -61,7 +66,7 @@ void plan_free_all(merbit_plan* p) {
                   p->bpart[4], p->bpart[5], p->bpart[6], p->sperm, p->scol, p->svals, p->swords,
                   p->yv[0], p->yv[1], p->range_tile, p->hot_off};
   for (void* b : bufs)
-    if (b) (void)hipFree(b);
+    if (b) dev_free(b);
   for (auto& ev : p->events) {
     (void)hipEventDestroy(ev.first);
     (void)hipEventDestroy(ev.second);
@@ -159,11 +164,11 @@ void invalidate_graphs(merbit_plan* p) {
 int ensure_dmask(merbit_plan* p, hipStream_t st) {
   if (p->dmask) return MERBIT_OK;
   unsigned char* bytes = nullptr;
-  HIP_TRY(hipMalloc(&p->dmask, sizeof(uint32_t) * (size_t)((p->n_cols + 31) / 32 + 1)));
-  HIP_TRY(hipMalloc(&bytes, (size_t)(p->n_cols > 0 ? p->n_cols : 1)));
+  HIP_TRY(dev_alloc(&p->dmask, sizeof(uint32_t) * (size_t)((p->n_cols + 31) / 32 + 1)));
+  HIP_TRY(dev_alloc(&bytes, (size_t)(p->n_cols > 0 ? p->n_cols : 1)));
   hipError_t e = launch_dangling_mask(p->col, p->nnz, p->n_cols, bytes, p->dmask, st);
   hipError_t e2 = hipStreamSynchronize(st);
-  (void)hipFree(bytes);
+  dev_free(bytes);
   if (e != hipSuccess) return fail_hip("dangling mask", e);
   if (e2 != hipSuccess) return fail_hip("dangling mask sync", e2);
   return MERBIT_OK;
@@ -174,15 +179,15 @@ int ensure_pagerank_state(merbit_plan* p, hipStream_t st) {
   int rc = ensure_dmask(p, st);
   if (rc != MERBIT_OK) return rc;
   if (!p->ybuf[0]) {
-    HIP_TRY(hipMalloc(&p->ybuf[0], vb));
-    HIP_TRY(hipMalloc(&p->ybuf[1], vb));
-    HIP_TRY(hipMalloc(&p->xwork, vb));
+    HIP_TRY(dev_alloc(&p->ybuf[0], vb));
+    HIP_TRY(dev_alloc(&p->ybuf[1], vb));
+    HIP_TRY(dev_alloc(&p->xwork, vb));
     p->zeroed_buf = -1;
   }
   if (!p->partials[0]) {
     p->reduce_grid = pr_reduce_grid(p->n_rows);
-    HIP_TRY(hipMalloc(&p->partials[0], 2 * sizeof(double) * (size_t)p->reduce_grid));
-    HIP_TRY(hipMalloc(&p->partials[1], 2 * sizeof(double) * (size_t)p->reduce_grid));
+    HIP_TRY(dev_alloc(&p->partials[0], 2 * sizeof(double) * (size_t)p->reduce_grid));
+    HIP_TRY(dev_alloc(&p->partials[1], 2 * sizeof(double) * (size_t)p->reduce_grid));
   }
   return MERBIT_OK;
 }
@@ -308,11 +313,11 @@ static int build_hot_cache(merbit_plan* p, int cap_req, hipStream_t st) {
     unsigned char* tmp = nullptr;
     auto release = [&]() {
       (void)hipStreamSynchronize(st);
-      if (tmp) (void)hipFree(tmp);
+      if (tmp) dev_free(tmp);
     };
-    hipError_t e = hipMalloc(&tmp, wb + sizeof(HotSel));
+    hipError_t e = dev_alloc(&tmp, wb + sizeof(HotSel));
     HotSel* sel_dev = reinterpret_cast<HotSel*>(tmp + wb);
-    if (e == hipSuccess) e = hipMalloc(&p->hot_cols, sizeof(int32_t) * (size_t)cap);
+    if (e == hipSuccess) e = dev_alloc(&p->hot_cols, sizeof(int32_t) * (size_t)cap);
     if (e == hipSuccess)
       e = hot_select_ranges(p->col, &seg, 1, cap, true, tmp, p->hot_cols, sel_dev, st);
     HotSel sel{};
@@ -329,13 +334,13 @@ static int build_hot_cache(merbit_plan* p, int cap_req, hipStream_t st) {
     if (p->hot_coverage > 1.0) p->hot_coverage = 1.0;
     const bool keep = taken > 0 && (cap_req > 0 || p->hot_coverage >= 0.2);
     if (keep) {
-      e = hipMalloc(&p->colx, sizeof(int32_t) * (size_t)p->nnz);
+      e = dev_alloc(&p->colx, sizeof(int32_t) * (size_t)p->nnz);
       if (e == hipSuccess) e = hot_recode_ranges(p->col, &seg, 1, tmp, p->colx, st);
-      if (e == hipSuccess) e = hipMalloc(&p->x_hot, vs * (size_t)taken);
+      if (e == hipSuccess) e = dev_alloc(&p->x_hot, vs * (size_t)taken);
       if (e == hipSuccess) p->hot_n = (int32_t)taken;
     } else {
       (void)hipStreamSynchronize(st);
-      (void)hipFree(p->hot_cols);
+      dev_free(p->hot_cols);
       p->hot_cols = nullptr;
     }
     release();
@@ -344,7 +349,7 @@ static int build_hot_cache(merbit_plan* p, int cap_req, hipStream_t st) {
   if (p->hot_n > 0) {
     if (p->hot_all) {
       // slot = column: the recoded stream is -1 - col
-      HIP_TRY(hipMalloc(&p->colx, sizeof(int32_t) * (size_t)p->nnz));
+      HIP_TRY(dev_alloc(&p->colx, sizeof(int32_t) * (size_t)p->nnz));
       HIP_TRY(hot_recode_all(p->col, p->nnz, p->colx, st));
     }
     p->hot_lds_bytes = vs * (size_t)p->hot_n;
@@ -362,11 +367,11 @@ int build_tile(merbit_plan* p, const int32_t* row_ptr, hipStream_t st) {
   const int sigma = p->sigma;
   p->tile_num = (L + (int64_t)kOmega * sigma - 1) / ((int64_t)kOmega * sigma);
   p->lane_num = (L + sigma - 1) / sigma;
-  HIP_TRY(hipMalloc(&p->tile_x, sizeof(int32_t) * (size_t)(p->tile_num + 1)));
-  HIP_TRY(hipMalloc(&p->tile_y, sizeof(uint32_t) * (size_t)(p->tile_num + 1)));
+  HIP_TRY(dev_alloc(&p->tile_x, sizeof(int32_t) * (size_t)(p->tile_num + 1)));
+  HIP_TRY(dev_alloc(&p->tile_y, sizeof(uint32_t) * (size_t)(p->tile_num + 1)));
   const size_t lanes = (size_t)(p->lane_num > 0 ? p->lane_num : 1);
-  if (p->desc_bits == 64) HIP_TRY(hipMalloc(&p->lane_desc64, sizeof(uint64_t) * lanes));
-  else HIP_TRY(hipMalloc(&p->lane_desc, sizeof(uint32_t) * lanes));
+  if (p->desc_bits == 64) HIP_TRY(dev_alloc(&p->lane_desc64, sizeof(uint64_t) * lanes));
+  else HIP_TRY(dev_alloc(&p->lane_desc, sizeof(uint32_t) * lanes));
   if (p->plan_rows == 0) {
     // empty path: TILE = {[0], [0]}
     HIP_TRY(hipMemsetAsync(p->tile_x, 0, sizeof(int32_t), st));
@@ -502,7 +507,7 @@ int merbit_plan_create(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     }                                          \
   } while (0)
 
-  CREATE_TRY(hipMalloc(&p->scratch, 64));
+  CREATE_TRY(dev_alloc(&p->scratch, 64));
   if (validate && (n_rows > 0 || nnz > 0)) {
     CREATE_TRY(hipMemsetAsync(p->scratch, 0, 64, st));
     CREATE_TRY(launch_validate(row_ptr, col_ind, n_rows, n_cols, nnz,

@@ -37,7 +37,7 @@ int merbit_transpose(merbit_plan* p, int32_t* rowT_ptr, int32_t* colT, int32_t* 
   int end_bit = 1;
   while (end_bit < 31 && ((int64_t)1 << end_bit) < p->n_cols) ++end_bit;
   void* tmp = nullptr;
-  hipError_t e = hipMalloc(&tmp, transpose_temp_bytes(m, end_bit));
+  hipError_t e = dev_alloc(&tmp, transpose_temp_bytes(m, end_bit));
   if (e == hipSuccess && m > 0) {
     TileRowsArgs a = tile_rows_args(p);
     a.rows = transpose_rows(m, end_bit, tmp, colT);
@@ -46,7 +46,7 @@ int merbit_transpose(merbit_plan* p, int32_t* rowT_ptr, int32_t* colT, int32_t* 
   if (e == hipSuccess)
     e = launch_transpose(p->col, m, p->n_cols, end_bit, tmp, rowT_ptr, colT, perm, st);
   (void)hipStreamSynchronize(st);
-  if (tmp) (void)hipFree(tmp);
+  if (tmp) dev_free(tmp);
   if (e != hipSuccess) return fail_hip("transpose", e);
   p->last_stream = st;
   return MERBIT_OK;

@@ -156,22 +156,22 @@ static int ensure_multi_tables(merbit_plan* p, const int64_t* graph_ptr, int n_g
   }
   void* old[] = {p->multi_chunk_row, p->multi_chunk_graph, p->multi_chunk_ptr, p->multi_gsize,
                  p->multi_part, p->multi_gsum[0], p->multi_gsum[1], p->multi_hot_graph};
-  HIP_TRY(hipStreamSynchronize(st));  // earlier calls may still read the old tables
+  HIP_TRY(hipDeviceSynchronize());  // earlier calls, on any stream, may still read the old tables
   invalidate_graphs(p);
   for (void* b : old)
-    if (b) (void)hipFree(b);
+    if (b) dev_free(b);
   p->multi_chunk_row = p->multi_chunk_graph = p->multi_chunk_ptr = nullptr;
   p->multi_gsize = p->multi_part = p->multi_gsum[0] = p->multi_gsum[1] = nullptr;
   p->multi_hot_graph = nullptr;
   p->multi_gp.clear();
   const size_t C = chunk_graph.size();
-  HIP_TRY(hipMalloc(&p->multi_chunk_row, sizeof(int32_t) * (C + 1)));
-  HIP_TRY(hipMalloc(&p->multi_chunk_graph, sizeof(int32_t) * C));
-  HIP_TRY(hipMalloc(&p->multi_chunk_ptr, sizeof(int32_t) * (size_t)(n_graphs + 1)));
-  HIP_TRY(hipMalloc(&p->multi_gsize, sizeof(double) * (size_t)n_graphs));
-  HIP_TRY(hipMalloc(&p->multi_part, sizeof(double) * 2 * C));
-  HIP_TRY(hipMalloc(&p->multi_gsum[0], sizeof(double) * 2 * (size_t)n_graphs));
-  HIP_TRY(hipMalloc(&p->multi_gsum[1], sizeof(double) * 2 * (size_t)n_graphs));
+  HIP_TRY(dev_alloc(&p->multi_chunk_row, sizeof(int32_t) * (C + 1)));
+  HIP_TRY(dev_alloc(&p->multi_chunk_graph, sizeof(int32_t) * C));
+  HIP_TRY(dev_alloc(&p->multi_chunk_ptr, sizeof(int32_t) * (size_t)(n_graphs + 1)));
+  HIP_TRY(dev_alloc(&p->multi_gsize, sizeof(double) * (size_t)n_graphs));
+  HIP_TRY(dev_alloc(&p->multi_part, sizeof(double) * 2 * C));
+  HIP_TRY(dev_alloc(&p->multi_gsum[0], sizeof(double) * 2 * (size_t)n_graphs));
+  HIP_TRY(dev_alloc(&p->multi_gsum[1], sizeof(double) * 2 * (size_t)n_graphs));
   HIP_TRY(hipMemcpy(p->multi_chunk_row, chunk_row.data(), sizeof(int32_t) * (C + 1),
                     hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(p->multi_chunk_graph, chunk_graph.data(), sizeof(int32_t) * C,
@@ -181,7 +181,7 @@ static int ensure_multi_tables(merbit_plan* p, const int64_t* graph_ptr, int n_g
   HIP_TRY(hipMemcpy(p->multi_gsize, gsize.data(), sizeof(double) * n_graphs,
                     hipMemcpyHostToDevice));
   if (!hot_graph.empty()) {
-    HIP_TRY(hipMalloc(&p->multi_hot_graph, sizeof(int32_t) * hot_graph.size()));
+    HIP_TRY(dev_alloc(&p->multi_hot_graph, sizeof(int32_t) * hot_graph.size()));
     HIP_TRY(hipMemcpy(p->multi_hot_graph, hot_graph.data(), sizeof(int32_t) * hot_graph.size(),
                       hipMemcpyHostToDevice));
   }
@@ -394,10 +394,10 @@ int merbit_bicgstab(merbit_plan* p, const void* b, void* x_inout, double tol, in
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t n = p->n_rows;
   if (!p->bvec[0]) {
-    for (int k = 0; k < 7; ++k) HIP_TRY(hipMalloc(&p->bvec[k], vsize(p->dtype) * (size_t)n));
+    for (int k = 0; k < 7; ++k) HIP_TRY(dev_alloc(&p->bvec[k], vsize(p->dtype) * (size_t)n));
     p->bicg_G = bicg_grid(n);
     for (int k = 0; k < 7; ++k)
-      HIP_TRY(hipMalloc(&p->bpart[k], sizeof(double) * 2 * (size_t)p->bicg_G));
+      HIP_TRY(dev_alloc(&p->bpart[k], sizeof(double) * 2 * (size_t)p->bicg_G));
   }
   // bvec: 0 r, 1 r^, 2 p, 3 v (even iterations), 4 v (odd), 5 s, 6 t
   // bpart: 0/1 (r^.r, r.r) by parity, 2/3 (r^.v, 0), 4/5 ((t,s), (t,t)), 6 (b.b, 0)

@@ -16,19 +16,18 @@ namespace {
 // again (the parts given before are dead: every user is on the build's one
 // stream, so later work is ordered after earlier reads), and a request
 // beyond the reserve gets an allocation of its own.  Everything is freed
-// when the build leaves: a hipFree of a large block costs about 0.3 ms
-// (R-MAT 22), so the build frees one.
+// when the build leaves (the build has waited for its stream by then).
 class Arena {
  public:
   Arena() = default;
   Arena(const Arena&) = delete;
   Arena& operator=(const Arena&) = delete;
   ~Arena() {
-    if (base_) (void)hipFree(base_);
-    for (void* b : extra_) (void)hipFree(b);
+    if (base_) dev_free(base_);
+    for (void* b : extra_) dev_free(b);
   }
   hipError_t reserve(size_t bytes) {
-    const hipError_t e = hipMalloc(&base_, bytes > 0 ? bytes : 1);
+    const hipError_t e = dev_alloc(&base_, bytes > 0 ? bytes : 1);
     cap_ = e == hipSuccess ? bytes : 0;
     return e;
   }
@@ -41,7 +40,7 @@ class Arena {
       return hipSuccess;
     }
     void* q = nullptr;
-    const hipError_t e = hipMalloc(&q, b > 0 ? b : 1);
+    const hipError_t e = dev_alloc(&q, b > 0 ? b : 1);
     if (e == hipSuccess) extra_.push_back(q);
     *out = static_cast<T*>(q);
     return e;
@@ -102,8 +101,8 @@ static int build_stripes(merbit_plan* p, const int32_t* row_ptr, hipStream_t st,
   HIP_TRY(tmp.get(&a.flag, (size_t)m));
   HIP_TRY(tmp.get(&a.vidx, (size_t)m));
   a.temp = split_temp;
-  HIP_TRY(hipMalloc(&p->sperm, sizeof(int32_t) * (size_t)m));
-  HIP_TRY(hipMalloc(&p->scol, sizeof(int32_t) * (size_t)m));
+  HIP_TRY(dev_alloc(&p->sperm, sizeof(int32_t) * (size_t)m));
+  HIP_TRY(dev_alloc(&p->scol, sizeof(int32_t) * (size_t)m));
   a.perm = p->sperm;
   a.col_s = p->scol;
   HIP_TRY(launch_stripe_split(a, st));
@@ -120,18 +119,18 @@ static int build_stripes(merbit_plan* p, const int32_t* row_ptr, hipStream_t st,
   HIP_TRY(tmp.get(&a.vrow_stripe, (size_t)nv));
   HIP_TRY(tmp.get(&a.wcnt, (size_t)nw));
   HIP_TRY(tmp.get(&a.rank, (size_t)nw));
-  HIP_TRY(hipMalloc(&p->swords, sizeof(StripeWord) * (size_t)nw));
+  HIP_TRY(dev_alloc(&p->swords, sizeof(StripeWord) * (size_t)nw));
   a.sw = p->swords;
   HIP_TRY(launch_stripe_rows(a, nv, st));
   // values in stacked order, the plan of A', and its two result buffers
-  HIP_TRY(hipMalloc(&p->svals, vsize(p->dtype) * (size_t)m));
+  HIP_TRY(dev_alloc(&p->svals, vsize(p->dtype) * (size_t)m));
   int rc = stripes_copy_values(p, p->values, st);
   if (rc != MERBIT_OK) return rc;
   rc = build_tile(p, a.vrow_ptr, st);
   if (rc != MERBIT_OK) return rc;
   const size_t yb = vsize(p->dtype) * (size_t)nv;
-  HIP_TRY(hipMalloc(&p->yv[0], yb));
-  HIP_TRY(hipMalloc(&p->yv[1], yb));
+  HIP_TRY(dev_alloc(&p->yv[0], yb));
+  HIP_TRY(dev_alloc(&p->yv[1], yb));
   // zero everywhere: in particular at every tile's first row (dual buffers)
   HIP_TRY(hipMemsetAsync(p->yv[0], 0, yb, st));
   HIP_TRY(hipMemsetAsync(p->yv[1], 0, yb, st));
@@ -199,8 +198,8 @@ static int build_range_hot(merbit_plan* p, int cap_req, hipStream_t st, Arena& t
     const int64_t nc = p->n_cols;
     unsigned char* work = nullptr;  // the selection's work space, a new part when a cut needs more
     size_t work_bytes = 0;
-    HIP_TRY(hipMalloc(&p->hot_cols, sizeof(int32_t) * (size_t)(cap * R)));
-    HIP_TRY(hipMalloc(&p->colx, sizeof(int32_t) * (size_t)p->nnz));
+    HIP_TRY(dev_alloc(&p->hot_cols, sizeof(int32_t) * (size_t)(cap * R)));
+    HIP_TRY(dev_alloc(&p->colx, sizeof(int32_t) * (size_t)p->nnz));
     std::vector<HotSel> sel((size_t)R);
     std::vector<HotSeg> segs((size_t)R);
     // hot sets of the current ranges: hoff, cov (hot nonzeros per range).
@@ -293,24 +292,24 @@ static int build_range_hot(merbit_plan* p, int cap_req, hipStream_t st, Arena& t
     for (int k = 0; k < R; ++k) covered += cov[k];
     p->hot_coverage = p->nnz > 0 ? covered / (double)p->nnz : 0.0;
     if (cap_req < 0 && p->hot_coverage < 0.2) {
-      (void)hipFree(p->hot_cols);
-      (void)hipFree(p->colx);
+      dev_free(p->hot_cols);
+      dev_free(p->colx);
       p->hot_cols = nullptr;
       p->colx = nullptr;
       std::fill(hoff.begin(), hoff.end(), 0);
       taken_max = 0;
     }
   }
-  HIP_TRY(hipMalloc(&p->range_tile, sizeof(int32_t) * (size_t)(R + 1)));
+  HIP_TRY(dev_alloc(&p->range_tile, sizeof(int32_t) * (size_t)(R + 1)));
   HIP_TRY(hipMemcpyAsync(p->range_tile, rt.data(), sizeof(int32_t) * (size_t)(R + 1),
                          hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMalloc(&p->hot_off, sizeof(int32_t) * (size_t)(R + 1)));
+  HIP_TRY(dev_alloc(&p->hot_off, sizeof(int32_t) * (size_t)(R + 1)));
   HIP_TRY(hipMemcpyAsync(p->hot_off, hoff.data(), sizeof(int32_t) * (size_t)(R + 1),
                          hipMemcpyHostToDevice, st));
   p->hot_n = hoff[R];
   p->hot_lds_bytes = (size_t)taken_max * vs;
   if (p->hot_n > 0) {
-    HIP_TRY(hipMalloc(&p->x_hot, vs * (size_t)p->hot_n));
+    HIP_TRY(dev_alloc(&p->x_hot, vs * (size_t)p->hot_n));
     HIP_TRY(spmv_wave_set_hot_lds(p->dtype, p->sigma, p->waves, p->hot_lds_bytes,
                                   p->desc_bits == 64));
   } else {

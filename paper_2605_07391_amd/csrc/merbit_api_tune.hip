@@ -38,9 +38,10 @@ int merbit_tune(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t* row_
   void *x = nullptr, *y0 = nullptr, *y1 = nullptr;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   auto cleanup = [&]() {
-    if (x) (void)hipFree(x);
-    if (y0) (void)hipFree(y0);
-    if (y1) (void)hipFree(y1);
+    (void)hipStreamSynchronize(st);  // x's fill, the last candidate's launches
+    if (x) dev_free(x);
+    if (y0) dev_free(y0);
+    if (y1) dev_free(y1);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
   };
@@ -52,9 +53,9 @@ int merbit_tune(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t* row_
       return fail_hip(#expr, _e);               \
     }                                           \
   } while (0)
-  TUNE_TRY(hipMalloc(&x, vs * width * (size_t)(n_cols > 0 ? n_cols : 1)));
-  TUNE_TRY(hipMalloc(&y0, vs * width * (size_t)(n_rows > 0 ? n_rows : 1)));
-  TUNE_TRY(hipMalloc(&y1, vs * width * (size_t)(n_rows > 0 ? n_rows : 1)));
+  TUNE_TRY(dev_alloc(&x, vs * width * (size_t)(n_cols > 0 ? n_cols : 1)));
+  TUNE_TRY(dev_alloc(&y0, vs * width * (size_t)(n_rows > 0 ? n_rows : 1)));
+  TUNE_TRY(dev_alloc(&y1, vs * width * (size_t)(n_rows > 0 ? n_rows : 1)));
   // x = 1.0f (F32) or the double with two 1.0f words (about 1.0000002, F64)
   TUNE_TRY(hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(x), 0x3f800000u,
                              (vs / 4) * width * (size_t)(n_cols > 0 ? n_cols : 1), st));

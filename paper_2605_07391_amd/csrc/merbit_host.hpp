@@ -133,6 +133,19 @@ int host_exception() noexcept;
 
 inline size_t vsize(int dtype) { return dtype == MERBIT_F64 ? sizeof(double) : sizeof(float); }
 
+// Device memory of plans and temporaries (merbit_mem.hip): freed blocks are
+// kept for reuse, within a bound.  Free a block only when no work that uses it
+// is pending on any stream.
+hipError_t dev_alloc_bytes(void** out, size_t bytes);
+template <typename T>
+hipError_t dev_alloc(T** out, size_t bytes) {
+  void* q = nullptr;
+  const hipError_t e = dev_alloc_bytes(&q, bytes);
+  *out = static_cast<T*>(q);
+  return e;
+}
+void dev_free(void* ptr) noexcept;
+
 void plan_free_all(merbit_plan* p);
 // The fused SpMV y = A x (z: the other dual buffer, cleared at boundary rows,
 // or nullptr).  hot_ready: the plan's hot-column copy already holds x's hot

@@ -451,3 +451,52 @@ def test_wave_tile_queue_across_launches(stripes, dtype):
             torch.cuda.synchronize()
             check_spmv(bufs[it % 2], rp, col, vals64, x64, dtype, f"dual {it}")
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+def test_plan_memory_reuse_over_streams_and_threads(dtype):
+    """Plans built, used and destroyed one after another and in two threads on
+    streams of their own, with matrices of equal and of different sizes, so
+    that each takes device memory which another has just given up: every y
+    must be the oracle's."""
+    import threading
+
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    mats = []
+    for seed, n in enumerate((3000, 3000, 700, 3000, 20000, 20000)):
+        rp, col = graphgen.chung_lu_pattern(n, 9 * n, 2.1, 0.1, seed=50 + seed)
+        vals = np.random.default_rng(seed).uniform(-1, 1, len(col))
+        mats.append((rp, col, vals, seeded_x(n, 70 + seed, dtype)))
+    got, errors = {}, []
+
+    def work(who, order):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for rep, k in enumerate(order):
+                    rp, col, vals, x64 = mats[k]
+                    n = len(rp) - 1
+                    r, c, v = to_device(rp, col, vals, dtype, dev)
+                    x = torch.from_numpy(x64).to(dtype).to(dev)
+                    plan = pkg.Plan(r, c, v, n, stripes=8 if rep % 3 == 2 else 0)
+                    y = plan.spmv(x)
+                    if rep % 2:
+                        plan.spmv(x, out=y)
+                    plan.close()
+                    got[who, rep] = (k, y.clone())
+            stream.synchronize()
+        except Exception as e:  # reported below, in the test's own thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(w, o))
+               for w, o in enumerate([(0, 1, 2, 3, 4, 5, 0, 4), (5, 4, 3, 2, 1, 0, 3, 5)])]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for (who, rep), (k, y) in got.items():
+        rp, col, vals, x64 = mats[k]
+        check_spmv(y, rp, col, host_values(vals, dtype), x64, dtype, f"thread {who} plan {rep}")
