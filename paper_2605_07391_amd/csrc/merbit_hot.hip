@@ -165,61 +165,98 @@ __device__ __forceinline__ int64_t block_exscan_i64(int64_t v, int64_t* s_wave, 
   return before + incl - v;
 }
 
-// Cut of a range's histogram (bins 1 .. kHotHistBins - 1; bin 0 = uncounted
-// columns).  Wavefronts sum the groups of 64 bins with coalesced loads;
-// thread i then owns group kCutGroups - 1 - i, so the scan in thread order
-// runs from the largest counts down.
-__global__ __launch_bounds__(kCutThreads) void select_cut_kernel(
-    const int32_t* __restrict__ hist_all, int64_t cap, int whole_ties,
-    HotSel* __restrict__ sel_all) {
-  constexpr int W = kCutThreads / kOmega;
-  __shared__ int64_t s_grp[kCutGroups];
-  __shared__ int64_t s_wave[W];
-  __shared__ int32_t s_cut;
-  __shared__ int64_t s_above;
-  const int32_t* hist = hist_all + (size_t)blockIdx.x * kHotHistBins;
-  const int lid = threadIdx.x & (kOmega - 1), wid = threadIdx.x / kOmega;
-  for (int g = wid; g < kCutGroups; g += W) {
-    const int b = g * kOmega + lid;
-    const int64_t s = wave_sum((int64_t)(b >= 1 ? hist[b] : 0));
-    if (lid == 0) s_grp[g] = s;
+// Per group of 64 bins of a range's histogram (bin 0, the uncounted columns,
+// left out): the number of columns and the sum of their counts.  A block sums
+// kGroupsPerBlock groups, 16 lanes with 16-byte loads per group.
+constexpr int kGroupsPerBlock = 16;
+
+__global__ __launch_bounds__(kGroupsPerBlock * 16) void hist_groups_kernel(
+    const int32_t* __restrict__ hist_all, int64_t* __restrict__ grp_all) {
+  const int32_t* hist = hist_all + (size_t)blockIdx.y * kHotHistBins;
+  int64_t* grp = grp_all + (size_t)blockIdx.y * kCutGroups * 2;
+  const int g = blockIdx.x * kGroupsPerBlock + threadIdx.x / 16;
+  const int b = g * kOmega + (threadIdx.x & 15) * 4;
+  int4 h = *reinterpret_cast<const int4*>(hist + b);
+  if (b == 0) h.x = 0;
+  int64_t n = (int64_t)h.x + h.y + ((int64_t)h.z + h.w);
+  int64_t c = (int64_t)b * h.x + (int64_t)(b + 1) * h.y + (int64_t)(b + 2) * h.z +
+              (int64_t)(b + 3) * h.w;
+#pragma unroll
+  for (int d = 8; d >= 1; d >>= 1) {
+    n += __shfl_xor(n, d, 16);
+    c += __shfl_xor(c, d, 16);
   }
-  __syncthreads();
+  if ((threadIdx.x & 15) == 0) {
+    grp[2 * g] = n;
+    grp[2 * g + 1] = c;
+  }
+}
+
+// Cut of a range's histogram.  Thread i owns group kCutGroups - 1 - i, so the
+// scan in thread order runs from the largest counts down; the first wavefront
+// then scans the bins of the cut's group.  What bounds it: one block's memory
+// round trips.  When this block read the histogram itself (256 KB through one
+// CU, twice, and the cut's group bin by bin) it took 58 us on R-MAT 20; the
+// groups summed over the chip first, the two launches take 9 us.
+__global__ __launch_bounds__(kCutThreads) void select_cut_kernel(
+    const int32_t* __restrict__ hist_all, const int64_t* __restrict__ grp_all, int64_t cap,
+    int whole_ties, HotSel* __restrict__ sel_all) {
+  constexpr int W = kCutThreads / kOmega;
+  __shared__ int64_t s_wave[W];
+  __shared__ int s_group;
+  __shared__ int32_t s_cut;
+  __shared__ int64_t s_above, s_part;
+  const int32_t* hist = hist_all + (size_t)blockIdx.x * kHotHistBins;
+  const int64_t* grp = grp_all + (size_t)blockIdx.x * kCutGroups * 2;
   const int g = kCutGroups - 1 - (int)threadIdx.x;
-  const int64_t mine = s_grp[g];
+  const int64_t mine = grp[2 * g], mine_cov = grp[2 * g + 1];
   int64_t tot = 0;
   const int64_t before = block_exscan_i64<kCutThreads>(mine, s_wave, &tot);
   if (threadIdx.x == 0) {
+    s_group = -1;
     s_cut = 0;  // no cut: every counted column fits
     s_above = tot;
+    s_part = 0;
   }
   __syncthreads();
   if (before <= cap && before + mine > cap) {
-    // the cut lies in this thread's group: the first bin from the top whose
-    // columns, with those above, exceed the cap
-    int64_t run = before;
-    const int lo = g * kOmega > 1 ? g * kOmega : 1;
-    for (int b = g * kOmega + kOmega - 1; b >= lo; --b) {
-      if (run + hist[b] > cap) {
-        s_cut = b;
-        s_above = run;
-        break;
+    s_group = g;
+    s_above = before;
+  }
+  __syncthreads();
+  const int gc = s_group;
+  if (gc >= 0 && threadIdx.x < kOmega) {
+    // the cut lies in group gc: the first bin from the top whose columns, with
+    // those above, exceed the cap
+    const int lid = (int)threadIdx.x;
+    const int b = gc * kOmega + kOmega - 1 - lid;
+    const int64_t c = b >= 1 ? hist[b] : 0;
+    int64_t incl = c, cov = (int64_t)b * c;
+#pragma unroll
+    for (int d = 1; d < kOmega; d <<= 1) {
+      const int64_t u = __shfl_up(incl, d, kOmega), v = __shfl_up(cov, d, kOmega);
+      if (lid >= d) {
+        incl += u;
+        cov += v;
       }
-      run += hist[b];
+    }
+    const int64_t base = s_above;
+    const unsigned long long over = __ballot(base + incl > cap);
+    if (over != 0 && lid == __builtin_ctzll(over)) {
+      s_cut = b;
+      s_above = base + incl - c;
+      s_part = cov - (int64_t)b * c;
     }
   }
   __syncthreads();
   const int32_t t = s_cut;
   const int64_t above = s_above;
   const int64_t extra = (t == 0 || whole_ties) ? 0 : cap - above;
-  // covered: the sum of the taken columns' counts
-  int64_t cov = 0;
-  for (int g2 = wid; g2 < kCutGroups; g2 += W) {
-    const int b = g2 * kOmega + lid;
-    cov += b > t ? (int64_t)b * hist[b] : 0;
-  }
+  // covered: the sum of the taken columns' counts, groups above the cut's and
+  // the part of its own
   int64_t cov_tot = 0;
-  (void)block_exscan_i64<kCutThreads>(cov, s_wave, &cov_tot);
+  (void)block_exscan_i64<kCutThreads>(g > gc ? mine_cov : 0, s_wave, &cov_tot);
+  cov_tot += s_part;
   if (threadIdx.x == 0) {
     HotSel* sel = sel_all + blockIdx.x;
     sel->t = t;
@@ -354,6 +391,8 @@ __global__ __launch_bounds__(kSelThreads) void select_assign_kernel(
   }
 }
 
+constexpr int kRecodeUnroll = 8;
+
 // colx[lo + k] = -1 - slot(col[lo + k]) for a hot column of range
 // blockIdx.y, col[lo + k] otherwise
 __global__ void recode_ranges_kernel(const int32_t* __restrict__ col,
@@ -364,11 +403,25 @@ __global__ void recode_ranges_kernel(const int32_t* __restrict__ col,
   const int32_t* in = col + sg.lo;
   int32_t* out = colx + sg.lo;
   const int32_t* slot_of = slot_all + sg.coff;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < sg.len; k += stride) {
-    const int32_t c = in[k];
-    const int32_t s = slot_of[c - sg.c_lo];
-    out[k] = s >= 0 ? -1 - s : c;
+  // kRecodeUnroll columns, then their slots, in flight per thread: bound by the
+  // scattered slot reads (8 against 1: 327 against 373 us on the stacked R-MAT
+  // 22, no difference on R-MAT 20)
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x * kRecodeUnroll;
+  for (int64_t k0 = (int64_t)blockIdx.x * blockDim.x * kRecodeUnroll + threadIdx.x; k0 < sg.len;
+       k0 += stride) {
+    int32_t c[kRecodeUnroll], s[kRecodeUnroll];
+#pragma unroll
+    for (int u = 0; u < kRecodeUnroll; ++u) {
+      const int64_t k = k0 + u * (int64_t)blockDim.x;
+      c[u] = k < sg.len ? __builtin_nontemporal_load(in + k) : sg.c_lo;
+    }
+#pragma unroll
+    for (int u = 0; u < kRecodeUnroll; ++u) s[u] = slot_of[c[u] - sg.c_lo];
+#pragma unroll
+    for (int u = 0; u < kRecodeUnroll; ++u) {
+      const int64_t k = k0 + u * (int64_t)blockDim.x;
+      if (k < sg.len) __builtin_nontemporal_store(s[u] >= 0 ? -1 - s[u] : c[u], out + k);
+    }
   }
 }
 
@@ -413,13 +466,14 @@ static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 // Work-space layout: the range table, the histograms, the counts, the slot
 // map, then the selection blocks' counts and plan.
 struct HotLayout {
-  size_t segs, hist, counts, slot, blocks, total;
+  size_t segs, groups, hist, counts, slot, blocks, total;
 };
 
 static HotLayout hot_layout(int R, int64_t span_sum, int64_t nb_sum) {
   HotLayout l;
   l.segs = 0;
-  l.hist = l.segs + align256(sizeof(HotSeg) * (size_t)R);
+  l.groups = l.segs + align256(sizeof(HotSeg) * (size_t)R);
+  l.hist = l.groups + align256(sizeof(int64_t) * 2 * kCutGroups * (size_t)R);
   l.counts = l.hist + align256(sizeof(int32_t) * kHotHistBins * (size_t)R);
   l.slot = l.counts + align256(sizeof(int32_t) * (size_t)span_sum);
   l.blocks = l.slot + align256(sizeof(int32_t) * (size_t)span_sum);
@@ -449,6 +503,7 @@ hipError_t hot_select_ranges(const int32_t* col, const HotSeg* segs, int R, int6
   const HotLayout l = hot_layout_of(segs, R);
   unsigned char* w = static_cast<unsigned char*>(work);
   HotSeg* segs_dev = reinterpret_cast<HotSeg*>(w + l.segs);
+  int64_t* groups = reinterpret_cast<int64_t*>(w + l.groups);
   int32_t* hist = reinterpret_cast<int32_t*>(w + l.hist);
   int32_t* counts = reinterpret_cast<int32_t*>(w + l.counts);
   int32_t* slot_of = reinterpret_cast<int32_t*>(w + l.slot);
@@ -474,8 +529,11 @@ hipError_t hot_select_ranges(const int32_t* col, const HotSeg* segs, int R, int6
   hipLaunchKernelGGL(count_hist_kernel, dim3(grid_for(max_span, 512), (unsigned)R), dim3(256), 0,
                      st, counts, segs_dev, hist);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(select_cut_kernel, dim3((unsigned)R), dim3(kCutThreads), 0, st, hist, cap,
-                     whole_ties ? 1 : 0, sel);
+  hipLaunchKernelGGL(hist_groups_kernel, dim3(kCutGroups / kGroupsPerBlock, (unsigned)R),
+                     dim3(kGroupsPerBlock * 16), 0, st, hist, groups);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(select_cut_kernel, dim3((unsigned)R), dim3(kCutThreads), 0, st, hist, groups,
+                     cap, whole_ties ? 1 : 0, sel);
   if ((e = hipGetLastError()) != hipSuccess || max_nb == 0) return e;
   hipLaunchKernelGGL(select_count_kernel, dim3((unsigned)max_nb, (unsigned)R), dim3(kSelThreads),
                      0, st, counts, segs_dev, sel, block_counts);
