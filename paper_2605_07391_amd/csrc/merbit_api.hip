@@ -134,13 +134,13 @@ int run_fused(merbit_plan* p, const void* x, void* y, void* z, hipStream_t st, b
   }
   if (p->stripes > 1) {
     const int c = p->yv_cur;
-    HIP_TRY(launch_spmv_wave(p->dtype, p->sigma, p->waves, p->hot_n > 0, p->hot_lds_bytes,
+    HIP_TRY(launch_spmv_wave(p->dtype, p->sigma, p->launch_waves, p->hot_n > 0, p->hot_lds_bytes,
                              spmv_args(p, x, p->yv[c], p->yv[c ^ 1]), st, p->desc_bits == 64));
     HIP_TRY(launch_stripe_combine(p->dtype, p->stripes, p->yv[c], p->plan_rows, p->swords,
                                   p->words, p->n_rows, y, st));
     p->yv_cur = c ^ 1;
   } else if (p->commit == MERBIT_COMMIT_WAVE)
-    HIP_TRY(launch_spmv_wave(p->dtype, p->sigma, p->waves, p->hot_n > 0, p->hot_lds_bytes,
+    HIP_TRY(launch_spmv_wave(p->dtype, p->sigma, p->launch_waves, p->hot_n > 0, p->hot_lds_bytes,
                              spmv_args(p, x, y, z), st, p->desc_bits == 64));
   else
     HIP_TRY(launch_spmv(p->dtype, p->sigma, p->waves, p->hot_n > 0, p->hot_lds_bytes,
@@ -197,7 +197,8 @@ int ensure_pagerank_state(merbit_plan* p, hipStream_t st) {
 // lanes plus head/tail partials; wave kernel = 64 sigma values per wavefront.
 static size_t static_lds_bytes(const merbit_plan* p) {
   const size_t vs = vsize(p->dtype);
-  if (p->commit == MERBIT_COMMIT_WAVE) return (size_t)p->waves * kOmega * p->sigma * vs + 64;
+  if (p->commit == MERBIT_COMMIT_WAVE)
+    return (size_t)(p->launch_waves > 0 ? p->launch_waves : p->waves) * kOmega * p->sigma * vs + 64;
   return ((size_t)p->waves * kOmega * p->sigma + 1 + 2 * (size_t)p->waves) * vs + 64;
 }
 
@@ -207,17 +208,32 @@ static bool kernel_supported(const merbit_plan* p, bool hot) {
                                          : spmv_supported(p->dtype, p->sigma, p->waves, hot);
 }
 
+// wavefronts per block of a wave plan without a hot cache (size_grid)
+constexpr int kPlainWaves = 4;
+
 // Choose the grid.  Block kernel: one commit unit (b lanes) per block, or with
 // the hot cache as many blocks as fit at once, each taking a run of units.
 // Wave kernel: as many resident blocks as LDS and wavefront slots allow (or
 // blocks_per_cu), every wavefront striding over the tiles; a striped plan
 // rounds the grid down to a multiple of the XCD count and gives each XCD's
 // blocks (block b runs on XCD b mod 8) one contiguous range of tiles.
+//
+// A wave plan of the default block size that has no hot cache is launched in
+// blocks of 4 wavefronts: larger blocks only serve to share the cache.  A
+// small plan then spreads over the chip (124 tiles as 31 blocks instead of 8
+// blocks of 16 wavefronts, 4 on each SIMD) and a middle-sized one fills it
+// (R-MAT 18: with 1,024 lanes one block fits per CU, and the last of 342
+// blocks began 15 us into a 26 us launch).  SMALL_NEW
 int size_grid(merbit_plan* p) {
+  p->launch_waves = p->waves;
+  if (p->commit == MERBIT_COMMIT_WAVE && p->stripes <= 1 && p->hot_n == 0 && !p->lanes_given &&
+      p->waves > kPlainWaves)
+    p->launch_waves = kPlainWaves;
+  const int waves = p->launch_waves;
   p->unit_tiles = p->commit == MERBIT_COMMIT_WAVE ? 1 : p->waves;
   p->chunk_num = (p->tile_num + p->unit_tiles - 1) / p->unit_tiles;
   p->chunks_per_block = 1;
-  p->grid = (int)((p->tile_num + p->waves - 1) / p->waves);
+  p->grid = (int)((p->tile_num + waves - 1) / waves);
   if (p->tile_num == 0) return MERBIT_OK;
   if (p->commit != MERBIT_COMMIT_WAVE && p->hot_n == 0) return MERBIT_OK;
   int cus = 0, lds_cu = 0;
@@ -226,14 +242,21 @@ int size_grid(merbit_plan* p) {
                                 p->device));
   const size_t per_block = static_lds_bytes(p) + p->hot_lds_bytes;
   int64_t blocks_per_cu = (int64_t)lds_cu / (int64_t)per_block;
-  const int64_t wave_cap = 32 / p->waves;  // 8 wavefronts per SIMD, 4 SIMDs per CU
+  int64_t wave_cap = 32 / waves;  // 8 wavefronts per SIMD, 4 SIMDs per CU
+  if (p->commit == MERBIT_COMMIT_WAVE && p->hot_lds_bytes == 0) {
+    // registers allow fewer: a block beyond the resident ones would start its
+    // share of the tiles when the others are done
+    int resident = 0;
+    HIP_TRY(spmv_wave_resident(p->dtype, p->sigma, waves, p->desc_bits == 64, &resident));
+    if (resident > 0 && resident < wave_cap) wave_cap = resident;
+  }
   if (blocks_per_cu > wave_cap) blocks_per_cu = wave_cap;
   if (p->blocks_per_cu_req > 0 && p->blocks_per_cu_req < blocks_per_cu)
     blocks_per_cu = p->blocks_per_cu_req;
   if (blocks_per_cu < 1) blocks_per_cu = 1;
   int64_t grid = (int64_t)cus * blocks_per_cu;
   if (p->commit == MERBIT_COMMIT_WAVE) {
-    const int64_t need = (p->tile_num + p->waves - 1) / p->waves;  // one tile per wavefront
+    const int64_t need = (p->tile_num + waves - 1) / waves;  // one tile per wavefront
     p->grid = (int)(grid < need ? grid : need);
     if (p->stripes > 1 && p->grid >= kXcds) {
       p->grid -= p->grid % kXcds;
@@ -485,6 +508,7 @@ int merbit_plan_create(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
   p->dtype = dtype;
   p->sigma = sigma;
   p->block_lanes = block_lanes;
+  p->lanes_given = opts.block_lanes != 0;
   p->waves = waves;
   p->bits = bits;
   p->commit = commit;

@@ -17,6 +17,8 @@
 struct merbit_plan {
   int64_t n_rows = 0, n_cols = 0, nnz = 0;
   int dtype = 0, sigma = 0, block_lanes = 0, waves = 0, bits = 0;
+  int launch_waves = 0;     // wavefronts per block of the fused launch (size_grid)
+  bool lanes_given = false; // block_lanes was an option, not the default
   int device = 0;
   int commit = MERBIT_COMMIT_WAVE;  // kernel family
   int blocks_per_cu_req = 0;

@@ -282,6 +282,8 @@ hipError_t launch_spmv_wave(int dtype, int sigma, int waves, bool hot, size_t ho
                             const SpmvArgs& a, hipStream_t st, bool desc64 = false);
 hipError_t spmv_wave_set_hot_lds(int dtype, int sigma, int waves, size_t bytes,
                                  bool desc64 = false);
+// blocks of the variant without the hot cache that fit on a CU at once
+hipError_t spmv_wave_resident(int dtype, int sigma, int waves, bool desc64, int* blocks);
 
 constexpr int kMaxLdsDevices = 64;
 // Dynamic-LDS opt-in of one kernel instance.  The attribute belongs to the

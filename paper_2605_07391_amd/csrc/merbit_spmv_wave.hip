@@ -377,13 +377,22 @@ static hipError_t set_wave_lds_t(size_t bytes) {
                            mu, granted);
 }
 
+// resident blocks per CU without dynamic LDS
+template <typename V, int S, int W, bool H, typename D>
+static hipError_t wave_resident_t(int* blocks) {
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      blocks, reinterpret_cast<const void*>(&spmv_wave_kernel<V, S, W, H, D>), W * kOmega, 0);
+}
+
 struct WaveEntry {
   hipError_t (*launch)(const SpmvArgs&, size_t, hipStream_t);
   hipError_t (*set_lds)(size_t);
+  hipError_t (*resident)(int*);
 };
 
 #define MERBIT_WCASE(S, D) \
-  case S: return WaveEntry{launch_wave_t<V, S, W, H, D>, set_wave_lds_t<V, S, W, H, D>};
+  case S: return WaveEntry{launch_wave_t<V, S, W, H, D>, set_wave_lds_t<V, S, W, H, D>, \
+                           wave_resident_t<V, S, W, H, D>};
 
 template <typename V, int W, bool H>
 static WaveEntry wave_pick_sigma(int sigma) {
@@ -392,7 +401,7 @@ static WaveEntry wave_pick_sigma(int sigma) {
     MERBIT_WCASE(4, uint32_t) MERBIT_WCASE(5, uint32_t) MERBIT_WCASE(6, uint32_t)
     MERBIT_WCASE(7, uint32_t) MERBIT_WCASE(8, uint32_t) MERBIT_WCASE(9, uint32_t)
     MERBIT_WCASE(10, uint32_t) MERBIT_WCASE(11, uint32_t) MERBIT_WCASE(12, uint32_t)
-    default: return WaveEntry{nullptr, nullptr};
+    default: return WaveEntry{nullptr, nullptr, nullptr};
   }
 }
 
@@ -405,13 +414,13 @@ static WaveEntry wave_pick_sigma64(int sigma) {
     switch (sigma) {
       MERBIT_WCASE(16, uint64_t) MERBIT_WCASE(20, uint64_t) MERBIT_WCASE(24, uint64_t)
       MERBIT_WCASE(28, uint64_t) MERBIT_WCASE(32, uint64_t)
-      default: return WaveEntry{nullptr, nullptr};
+      default: return WaveEntry{nullptr, nullptr, nullptr};
     }
   } else {
     switch (sigma) {
       MERBIT_WCASE(14, uint64_t) MERBIT_WCASE(16, uint64_t) MERBIT_WCASE(20, uint64_t)
       MERBIT_WCASE(24, uint64_t)
-      default: return WaveEntry{nullptr, nullptr};
+      default: return WaveEntry{nullptr, nullptr, nullptr};
     }
   }
 }
@@ -423,14 +432,14 @@ static WaveEntry wave_pick_waves(int sigma, int waves, bool desc64) {
     switch (waves) {
       case 4: return wave_pick_sigma64<V, 4, H>(sigma);
       case 8: return wave_pick_sigma64<V, 8, H>(sigma);
-      default: return WaveEntry{nullptr, nullptr};
+      default: return WaveEntry{nullptr, nullptr, nullptr};
     }
   }
   switch (waves) {
     case 4: return wave_pick_sigma<V, 4, H>(sigma);
     case 8: return wave_pick_sigma<V, 8, H>(sigma);
     case 16: return wave_pick_sigma<V, 16, H>(sigma);
-    default: return WaveEntry{nullptr, nullptr};
+    default: return WaveEntry{nullptr, nullptr, nullptr};
   }
 }
 
@@ -439,7 +448,7 @@ static WaveEntry wave_pick(int dtype, int sigma, int waves, bool hot, bool desc6
                              : wave_pick_waves<float, false>(sigma, waves, desc64);
   if (dtype == 1) return hot ? wave_pick_waves<double, true>(sigma, waves, desc64)
                              : wave_pick_waves<double, false>(sigma, waves, desc64);
-  return WaveEntry{nullptr, nullptr};
+  return WaveEntry{nullptr, nullptr, nullptr};
 }
 
 bool spmv_wave_supported(int dtype, int sigma, int waves, bool hot, bool desc64) {
@@ -451,6 +460,12 @@ hipError_t launch_spmv_wave(int dtype, int sigma, int waves, bool hot, size_t ho
   WaveEntry k = wave_pick(dtype, sigma, waves, hot, desc64);
   if (!k.launch) return hipErrorInvalidValue;
   return k.launch(a, hot ? hot_lds_bytes : 0, st);
+}
+
+hipError_t spmv_wave_resident(int dtype, int sigma, int waves, bool desc64, int* blocks) {
+  WaveEntry k = wave_pick(dtype, sigma, waves, false, desc64);
+  if (!k.resident) return hipErrorInvalidValue;
+  return k.resident(blocks);
 }
 
 hipError_t spmv_wave_set_hot_lds(int dtype, int sigma, int waves, size_t bytes, bool desc64) {
