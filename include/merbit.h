@@ -198,7 +198,9 @@ int merbit_plan_export(merbit_plan* plan, int32_t* tile_x, uint32_t* tile_y,
 /* y <- A x (Sec. 4.2, Algorithm "MERBIT SpMV"), overwriting y whatever it
  * held.  x: device [n_cols], y: device [n_rows], both of the plan's dtype, not
  * aliased.  Launches: a scatter that zeroes y at the first row of every commit
- * unit, the hot-value gather (partial hot cache only), then the fused kernel. */
+ * unit (not for a validated WAVE plan whose rows all have at most 128
+ * nonzeros), the hot-value gather (partial hot cache only), then the fused
+ * kernel. */
 int merbit_spmv(merbit_plan* plan, const void* x, void* y, void* stream);
 
 /* Dual-buffer form (Sec. 4.2, optimisation (3)): the fused launch only (plus

@@ -56,7 +56,7 @@ void plan_free_all(merbit_plan* p) {
   if (other) (void)hipSetDevice(dev);
   drop_graphs(p);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
-  void* bufs[] = {p->tile_x, p->tile_y, p->lane_desc, p->lane_desc64, p->scratch, p->dmask,
+  void* bufs[] = {p->tile_x, p->tile_y, p->row_start, p->lane_desc, p->lane_desc64, p->scratch, p->dmask,
                   p->ybuf[0], p->ybuf[1], p->xwork, p->partials[0], p->partials[1], p->hot_cols,
                   p->colx, p->x_hot, p->pbuf[0], p->pbuf[1], p->pbuf[2], p->ppart, p->psums[0],
                   p->psums[1], p->psrc, p->multi_chunk_row, p->multi_chunk_graph,
@@ -94,6 +94,7 @@ static SpmvArgs spmv_args(const merbit_plan* p, const void* x, void* y, void* z)
   a.chunks_per_block = p->chunks_per_block;
   a.grid = p->grid;
   a.hot_n = p->hot_n;
+  a.row_start = p->row_start;
   a.ranges = p->ranges;
   a.range_tile = p->range_tile;
   a.hot_off = p->hot_off;
@@ -139,10 +140,10 @@ int run_fused(merbit_plan* p, const void* x, void* y, void* z, hipStream_t st, b
     HIP_TRY(launch_stripe_combine(p->dtype, p->stripes, p->yv[c], p->plan_rows, p->swords,
                                   p->words, p->n_rows, y, st));
     p->yv_cur = c ^ 1;
-  } else if (p->commit == MERBIT_COMMIT_WAVE)
+  } else if (p->commit == MERBIT_COMMIT_WAVE) {
     HIP_TRY(launch_spmv_wave(p->dtype, p->sigma, p->launch_waves, p->hot_n > 0, p->hot_lds_bytes,
                              spmv_args(p, x, y, z), st, p->desc_bits == 64));
-  else
+  } else
     HIP_TRY(launch_spmv(p->dtype, p->sigma, p->waves, p->hot_n > 0, p->hot_lds_bytes,
                         spmv_args(p, x, y, z), st));
   if (events) HIP_TRY(hipEventRecord(e1, st));
@@ -392,6 +393,8 @@ int build_tile(merbit_plan* p, const int32_t* row_ptr, hipStream_t st) {
   p->lane_num = (L + sigma - 1) / sigma;
   HIP_TRY(dev_alloc(&p->tile_x, sizeof(int32_t) * (size_t)(p->tile_num + 1)));
   HIP_TRY(dev_alloc(&p->tile_y, sizeof(uint32_t) * (size_t)(p->tile_num + 1)));
+  if (p->commit == MERBIT_COMMIT_WAVE)
+    HIP_TRY(dev_alloc(&p->row_start, sizeof(int32_t) * (size_t)(p->tile_num + 1)));
   const size_t lanes = (size_t)(p->lane_num > 0 ? p->lane_num : 1);
   if (p->desc_bits == 64) HIP_TRY(dev_alloc(&p->lane_desc64, sizeof(uint64_t) * lanes));
   else HIP_TRY(dev_alloc(&p->lane_desc, sizeof(uint32_t) * lanes));
@@ -411,6 +414,7 @@ int build_tile(merbit_plan* p, const int32_t* row_ptr, hipStream_t st) {
   pa.tile_num = p->tile_num;
   pa.tile_x = p->tile_x;
   pa.tile_y = p->tile_y;
+  pa.row_start = p->row_start;
   pa.lane_desc = p->lane_desc;
   pa.lane_desc64 = p->lane_desc64;
   HIP_TRY(launch_plan(pa, st));
@@ -536,9 +540,11 @@ int merbit_plan_create(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     CREATE_TRY(hipMemsetAsync(p->scratch, 0, 64, st));
     CREATE_TRY(launch_validate(row_ptr, col_ind, n_rows, n_cols, nnz,
                                reinterpret_cast<unsigned*>(p->scratch), st));
-    unsigned flags = 0;
-    CREATE_TRY(hipMemcpyAsync(&flags, p->scratch, sizeof(unsigned), hipMemcpyDeviceToHost, st));
+    unsigned found[2] = {0, 0};
+    CREATE_TRY(hipMemcpyAsync(found, p->scratch, sizeof found, hipMemcpyDeviceToHost, st));
     CREATE_TRY(hipStreamSynchronize(st));
+    const unsigned flags = found[0];
+    p->longest_row = found[1];
     if (flags) {
       char buf[160];
       snprintf(buf, sizeof buf, "CSR validation failed:%s%s%s%s",
@@ -667,8 +673,12 @@ int merbit_spmv(merbit_plan* p, const void* x, void* y, void* stream) try {
   if (!y || (p->nnz > 0 && !x)) return fail(MERBIT_EINVAL, "x or y is NULL");
   if (x == y) return fail(MERBIT_EINVAL, "x and y alias");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int rc = zero_boundary(p, y, st);
-  if (rc != MERBIT_OK) return rc;
+  // without long rows the wave kernel stores every row and y needs no zeros
+  // (the longest row is known only of a validated plan)
+  if (p->row_start == nullptr || p->longest_row < 0 || p->longest_row > kOwnRowMax) {
+    const int rc = zero_boundary(p, y, st);
+    if (rc != MERBIT_OK) return rc;
+  }
   return run_fused(p, x, y, nullptr, st);
 } catch (...) {
   return merbit::host_exception();

@@ -303,6 +303,7 @@ static int build_range_hot(merbit_plan* p, int cap_req, hipStream_t st, Arena& t
   HIP_TRY(dev_alloc(&p->range_tile, sizeof(int32_t) * (size_t)(R + 1)));
   HIP_TRY(hipMemcpyAsync(p->range_tile, rt.data(), sizeof(int32_t) * (size_t)(R + 1),
                          hipMemcpyHostToDevice, st));
+  HIP_TRY(launch_split_ranges(p->tile_y, p->tile_num, p->range_tile, R, p->row_start, st));
   HIP_TRY(dev_alloc(&p->hot_off, sizeof(int32_t) * (size_t)(R + 1)));
   HIP_TRY(hipMemcpyAsync(p->hot_off, hoff.data(), sizeof(int32_t) * (size_t)(R + 1),
                          hipMemcpyHostToDevice, st));

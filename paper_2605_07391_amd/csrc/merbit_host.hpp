@@ -28,12 +28,14 @@ struct merbit_plan {
   int grid = 0, chunks_per_block = 1;
   int32_t* tile_x = nullptr;
   uint32_t* tile_y = nullptr;
+  int32_t* row_start = nullptr;  // [tile_num + 1], wave commit (SpmvArgs)
   uint32_t* lane_desc = nullptr;
   uint64_t* lane_desc64 = nullptr;  // set instead of lane_desc for 64-bit descriptors
   int desc_bits = 32;
   const int32_t* col = nullptr;
   const void* values = nullptr;
   hipStream_t last_stream = nullptr;
+  int64_t longest_row = -1;  // nonzeros of the longest row; -1: not validated
   // small device scratch: [0] validation flags / fast-tile count
   unsigned long long* scratch = nullptr;
   // hot-column x cache (hot_n > 0: the fused kernel reads col from colx)

@@ -189,6 +189,11 @@ __device__ __forceinline__ void block_sum2(double& a, double& b) {
   }
 }
 
+// nonzeros of a row up to which the tile it ends in finishes it alone.  An
+// atomic pair per tile costs more than reading half such a row again: see
+// merbit_spmv_wave.hip.
+constexpr int kOwnRowMax = 128;
+
 struct PlanArgs {
   const int32_t* row_ptr;
   int32_t n_rows;
@@ -199,6 +204,7 @@ struct PlanArgs {
   int64_t tile_num;
   int32_t* tile_x;
   uint32_t* tile_y;
+  int32_t* row_start;       // [tile_num + 1] see SpmvArgs, or nullptr
   uint32_t* lane_desc;      // 32-bit descriptors, or
   uint64_t* lane_desc64;    // 64-bit descriptors (exactly one is set)
 };
@@ -222,6 +228,12 @@ struct SpmvArgs {
   int32_t chunks_per_block;
   int32_t grid;
   int32_t hot_n;
+  // wave kernel, [tile_num + 1]: first nonzero of each tile's first row, -1 if
+  // that row has more than kOwnRowMax nonzeros or crosses into another range
+  // (0 after the last tile).  The
+  // tile a short row ends in writes it whole, adding up the part before the
+  // tile itself; only long rows are added to y and need it zero.
+  const int32_t* row_start;
   // wave kernel: tiles split into `ranges` contiguous parts (1: one part);
   // block b works on part b % ranges, whose tiles are
   // [range_tile[k], range_tile[k + 1]) and whose hot x values are
@@ -262,11 +274,16 @@ struct SpmmArgs {
   int32_t dmask_words;     // ceil(n_rows / 32)
 };
 
-// CSR checks; *flags gets bit 0: row_ptr[0] != 0, bit 1: row_ptr[n] != nnz,
-// bit 2: row_ptr decreasing, bit 3: column out of range.
+// CSR checks; flags[0] gets bit 0: row_ptr[0] != 0, bit 1: row_ptr[n] != nnz,
+// bit 2: row_ptr decreasing, bit 3: column out of range; flags[1] the longest
+// row's nonzeros.  Both zero before.
 hipError_t launch_validate(const int32_t* row_ptr, const int32_t* col, int64_t n_rows,
                            int64_t n_cols, int64_t nnz, unsigned* flags, hipStream_t st);
 hipError_t launch_plan(const PlanArgs& a, hipStream_t st);
+// rows that cross a cut between tile ranges count as long (row_start = -1)
+hipError_t launch_split_ranges(const uint32_t* tile_y, int64_t tile_num,
+                               const int32_t* range_tile, int ranges, int32_t* row_start,
+                               hipStream_t st);
 hipError_t launch_count_fast(const uint32_t* tile_y, int64_t tile_num,
                              unsigned long long* count, hipStream_t st);
 

@@ -23,18 +23,29 @@ __global__ void validate_kernel(const int32_t* __restrict__ row_ptr,
                                 const int32_t* __restrict__ col, int64_t n_rows, int64_t n_cols,
                                 int64_t nnz, unsigned* __restrict__ flags) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  unsigned f = 0;
+  unsigned f = 0, longest = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n_rows; i += stride) {
     const int32_t v = row_ptr[i];
     if (i == 0 && v != 0) f |= 1u;
     if (i == n_rows && (int64_t)v != nnz) f |= 2u;
-    if (i < n_rows && v > row_ptr[i + 1]) f |= 4u;
+    if (i < n_rows) {
+      const int32_t next = row_ptr[i + 1];
+      if (v > next) f |= 4u;
+      else longest = max(longest, (unsigned)next - (unsigned)v);
+    }
   }
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nnz; k += stride) {
     const int32_t c = col[k];
     if (c < 0 || (int64_t)c >= n_cols) f |= 8u;
   }
   if (f) atomicOr(flags, f);
+  // one atomic per block, and only where it may change the maximum
+  __shared__ unsigned s_longest;
+  if (threadIdx.x == 0) s_longest = 0;
+  __syncthreads();
+  if (longest > 0) atomicMax(&s_longest, longest);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_longest > flags[1]) atomicMax(&flags[1], s_longest);
 }
 
 hipError_t launch_validate(const int32_t* row_ptr, const int32_t* col, int64_t n_rows,
@@ -90,10 +101,20 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, D* __restrict__ l
       const int64_t i = j / kOmega;
       a.tile_x[i] = tx;
       a.tile_y[i] = (uint32_t)ty | (single_row ? kFastBit : 0u);
+      if (a.row_start != nullptr) {
+        // (the bounds hold for any valid row_ptr; one that was never validated
+        // must not send the SpMV out of its arrays)
+        const int32_t start = a.row_ptr[ty];
+        const int32_t len = ty < a.n_rows ? a.row_ptr[ty + 1] - start : 0;
+        const bool own = len >= 0 && len <= kOwnRowMax && start >= 0 && start <= tx &&
+                         tx - start <= kOwnRowMax;
+        a.row_start[i] = own ? start : -1;
+      }
     }
   } else if (j == a.lane_num) {
     a.tile_x[a.tile_num] = a.nnz;
     a.tile_y[a.tile_num] = (uint32_t)a.n_rows;
+    if (a.row_start != nullptr) a.row_start[a.tile_num] = 0;
   }
 }
 
@@ -106,6 +127,32 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t st) {
   else
     hipLaunchKernelGGL(plan_kernel<uint32_t>, dim3((unsigned)grid), dim3(256), 0, st, a,
                        a.lane_desc);
+  return hipGetLastError();
+}
+
+// A short row that crosses from one tile range into the next is treated as a
+// long one (row_start = -1 for every tile that begins in it): the column stream
+// before a range is recoded with another range's hot slots, so the tile the row
+// ends in cannot add up its beginning.
+__global__ void split_ranges_kernel(const uint32_t* __restrict__ tile_y, int64_t tile_num,
+                                    const int32_t* __restrict__ range_tile, int ranges,
+                                    int32_t* __restrict__ row_start) {
+  const int k = threadIdx.x + 1;  // the cut before range k
+  if (k >= ranges) return;
+  const int64_t t = range_tile[k];
+  if (t <= 0 || t >= tile_num || row_start[t] < 0) return;
+  const uint32_t r = tile_y[t] & kRowMask;
+  for (int64_t u = t; u >= 0 && (tile_y[u] & kRowMask) == r; --u) row_start[u] = -1;
+  for (int64_t u = t + 1; u < tile_num && (tile_y[u] & kRowMask) == r; ++u) row_start[u] = -1;
+}
+
+hipError_t launch_split_ranges(const uint32_t* tile_y, int64_t tile_num,
+                               const int32_t* range_tile, int ranges, int32_t* row_start,
+                               hipStream_t st) {
+  if (ranges <= 1) return hipSuccess;
+  if (ranges > kOmega) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(split_ranges_kernel, dim3(1), dim3(kOmega), 0, st, tile_y, tile_num,
+                     range_tile, ranges, row_start);
   return hipGetLastError();
 }
 

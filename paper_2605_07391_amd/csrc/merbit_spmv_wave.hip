@@ -9,10 +9,12 @@
 // each other:
 //   - rows that start and end inside a tile are complete after the tile's own
 //     scan and are stored with coalesced writes from the wavefront's LDS slots;
-//   - the tile's first row and last row may continue in neighbouring tiles and
-//     are added atomically to y, which is zero at every tile's first row before
-//     the launch (dual buffer: each tile zeroes z at its first row, Sec. 4.2
-//     opt. (3)).
+//   - a short row (at most kOwnRowMax nonzeros) that begins before the tile is
+//     finished by the tile it ends in, which adds up the few nonzeros before it
+//     again, and is stored like the others;
+//   - a long row that crosses tiles is added to y atomically by each of them; y
+//     is zero at every tile's first row before the launch (dual buffer: each
+//     tile zeroes z at its first row, Sec. 4.2 opt. (3)).
 // A block of WAVES wavefronts is resident for the whole launch.  The tiles
 // (with the tiles split into ranges, those of the block's range) are dealt
 // round robin over the blocks, and a block's wavefronts take the block's tiles
@@ -34,7 +36,10 @@
 // slower; a software pipeline that issues the next tile's gathers before the
 // current walk, and gathers split from the LDS reads (buffer loads, or loads
 // under a branch, where the compiler now merges both into one flat load) made
-// no difference.
+// no difference.  Short rows that cross tiles finished by one tile, with no
+// atomics (an atomic pair per tile) and, where no row is long, no launch that
+// zeroes y first: Chung-Lu 700,001 FP64 53.5 -> 45 us, 1,000,000 vertices of
+// degree 80 FP64 392 -> 346 us, 10,000 vertices FP32 10.6 -> 7.5 us.
 //
 // HOT: the block first copies the hot x values into LDS (the plan's recoded
 // column stream marks hot columns as -1 - slot) and serves those gathers from
@@ -53,6 +58,13 @@ struct WaveTile {
   D desc;
   int cc[SIGMA];
   V vv[SIGMA];
+  // first nonzero of the tile's first row (-1: a long row) and whether the
+  // row it ends in is short; the part of a short first row that lies before
+  // the tile is x_ws - hd nonzeros, lane l holding the l-th
+  int hd;
+  bool last_short;
+  int pc;
+  V pv;
 };
 
 template <typename D>
@@ -71,6 +83,17 @@ __device__ __forceinline__ uint64_t load_desc<uint64_t>(const SpmvArgs& a, int j
 // slower by 2 % for FP64 with 32-bit descriptors, which keeps plain loads.
 template <typename V, typename D>
 constexpr bool kBufferStream = sizeof(V) == 4 || sizeof(D) == 8;
+// How a gather picks LDS (hot columns) or memory: one flat load from a selected
+// address, or a load from memory for every lane (hot ones repeat x[0]) and one
+// from LDS.  The flat load is faster (sigma 28 FP32 on R-MAT 22: 199 against
+// 203 us per SpMV; sigma 24 FP64 306 against 322) but for FP64 with 64-bit
+// descriptors of sigma 14 and 16 (305 against 285 us).  Written as a branch,
+// the compiler emits the flat load in some instances and in others a global
+// and an LDS load into one register, each waiting for the one before (sigma 16
+// FP32: 297 against 213 us).
+template <typename V, int SIGMA, typename D>
+constexpr bool kFlatGather = sizeof(V) == 4 || sizeof(D) == 4 || SIGMA > 16;
+
 // word 3 of a raw (unformatted, stride 0) buffer resource on gfx950
 constexpr int kBufferWord3 = 0x00020000;
 // cache policy bits of a gfx950 buffer load: nt (streaming, evicted first)
@@ -99,6 +122,14 @@ __device__ __forceinline__ void wave_load_tile(const SpmvArgs& a, const int32_t*
   s.x_se = const_load(a.tile_x, t + 1) - s.x_ws;
   s.tyw = const_load(a.tile_y, t);
   s.y_we = (int)(const_load(a.tile_y, t + 1) & kRowMask);
+  s.hd = const_load(a.row_start, t);
+  s.last_short = const_load(a.row_start, t + 1) >= 0;
+  s.pc = 0;
+  s.pv = V(0);
+  if (s.hd >= 0 && lid < s.x_ws - s.hd) {
+    s.pc = col[s.hd + lid];
+    s.pv = val[s.hd + lid];
+  }
   const bool normal = s.x_se > 0 && !(s.tyw & kFastBit);
   s.desc = 0;
   if (normal) s.desc = load_desc<D>(a, min(t * kOmega + lid, a.lane_num - 1));
@@ -232,6 +263,22 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
     const int tile = t_begin + i * slots + slot;
     return tile < t_end ? tile : t_end;
   };
+  // x of column c, or for a hot column (kFlatGather off) an x value that x_of
+  // replaces by the one in LDS
+  auto gather = [&](int c) -> V {
+    if constexpr (HOT && kFlatGather<V, SIGMA, D>) {
+      const V* p = c < 0 ? s_hot + (-1 - c) : x + c;
+      return *p;
+    }
+    return x[HOT ? max(c, 0) : c];
+  };
+  auto x_of = [&](int c, V g) -> V {
+    if constexpr (HOT && !kFlatGather<V, SIGMA, D>) {
+      const V h = s_hot[c < 0 ? -1 - c : 0];
+      return c < 0 ? h : g;
+    }
+    return g;
+  };
   int t = tile_at(wid);
   int tn = t_end;
   WaveTile<V, SIGMA, D> cur;
@@ -246,15 +293,13 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
     if (cur.x_se > 0) {
 #pragma unroll
       for (int it = 0; it < SIGMA; ++it) {
-        const int c = cur.cc[it];
-        if (HOT) {
-          if (c >= 0) g[it] = x[c];
-          else g[it] = s_hot[-1 - c];
-        } else {
-          g[it] = x[c];
-        }
+        g[it] = gather(cur.cc[it]);
       }
     }
+    // (x is not empty if the first row has nonzeros before the tile)
+    const int before = cur.hd >= 0 ? cur.x_ws - cur.hd : 0;
+    V pg = V(0);
+    if (before > 0) pg = gather(cur.pc);
     // the tile after next, then the loads of the next tile: both go out
     // before the gathers are consumed
     int q = 0;
@@ -265,23 +310,34 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
     const int x_se = cur.x_se;
     const int y_ws = (int)(cur.tyw & kRowMask);
     const int y_we = cur.y_we;
+    const bool last_short = cur.last_short;
+    const bool own = cur.hd >= 0;  // this tile finishes its first row by itself
+    V pre = V(0);
+    if (before > 0) {
+      pre = cur.pv * x_of(cur.pc, pg);  // lanes past `before` hold a zero value and a gather of x[0]
+      if (lid >= before) pre = V(0);
+      for (int k = kOmega + lid; k < before; k += kOmega)
+        pre += val[cur.hd + k] * x_of(col[cur.hd + k], gather(col[cur.hd + k]));
+      pre = wave_total(pre);
+    }
     if (x_se == 0) {
       // down steps only: the rows strictly inside the tile are empty
       for (int r = y_ws + 1 + lid; r < y_we; r += kOmega) y[r] = V(0);
+      if (own && lid == 0 && y_we > y_ws) y[y_ws] = pre;
     } else if (cur.tyw & kFastBit) {
       // single-row tile (Sec. 4.2 opt. (1))
       V acc = V(0);
 #pragma unroll
       for (int it = 0; it < SIGMA; ++it)
-        if (lid + it * kOmega < x_se) acc += cur.vv[it] * g[it];
+        if (lid + it * kOmega < x_se) acc += cur.vv[it] * x_of(cur.cc[it], g[it]);
       acc = wave_total(acc);
-      if (lid == 0) global_add(&y[y_ws], acc);
+      if (lid == 0 && !own) global_add(&y[y_ws], acc);
     } else {
       wave_lds_sync();  // the previous tile's commit has read its slots
 #pragma unroll
       for (int it = 0; it < SIGMA; ++it) {
         const int k = lid + it * kOmega;
-        if (k < x_se) s_w[k] = cur.vv[it] * g[it];
+        if (k < x_se) s_w[k] = cur.vv[it] * x_of(cur.cc[it], g[it]);
       }
       wave_lds_sync();
       // walk (Algorithm tile_normal_tackle): the row that ends at a down step
@@ -346,11 +402,13 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
         // the first row that ends in this lane may begin in lanes before it
         V* slot = s_w + x_se + start_off;
         const V row_val = *slot + (lid > 0 ? carry : V(0));
-        if (start_off == 0) global_add(&y[y_ws], row_val);  // the tile's first row
-        else *slot = row_val;                               // begun inside the tile
+        if (start_off != 0) *slot = row_val;       // begun inside the tile
+        else if (own) y[y_ws] = pre + row_val;     // the tile's first row
+        else global_add(&y[y_ws], row_val);
       }
       // the last segment belongs to the row the tile ends in
-      if (lid == kOmega - 1 && y_we < a.n_rows && scan != V(0)) global_add(&y[y_we], scan);
+      if (lid == kOmega - 1 && !last_short && y_we < a.n_rows && scan != V(0))
+        global_add(&y[y_we], scan);
       wave_lds_sync();
       for (int r = lid + 1; r < y_we - y_ws; r += kOmega) y[y_ws + r] = s_w[x_se + r];
     }

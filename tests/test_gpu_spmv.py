@@ -500,3 +500,47 @@ def test_plan_memory_reuse_over_streams_and_threads(dtype):
     for (who, rep), (k, y) in got.items():
         rp, col, vals, x64 = mats[k]
         check_spmv(y, rp, col, host_values(vals, dtype), x64, dtype, f"thread {who} plan {rep}")
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+@pytest.mark.parametrize("sigma,desc_bits", [(1, 32), (2, 32), (7, 32), (12, 32), (16, 64)])
+@pytest.mark.parametrize("stripes,hot", [(0, 0), (0, 40), (8, 0), (8, 40)])
+@pytest.mark.parametrize("longest", [128, 129, 3000])
+def test_rows_finished_by_the_tile_they_end_in(longest, stripes, hot, sigma, desc_bits, dtype):
+    """Rows of at most 128 nonzeros that cross tiles (several tiles at sigma 1)
+    or tile ranges are finished by the tile they end in, longer ones by atomic
+    additions: lengths on both sides of the limit, empty rows at tile starts,
+    a y full of NaN, repeated calls, and a plan that was not validated."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    rng = np.random.default_rng(7 * sigma + stripes)
+    near = [127, 128, min(longest, 129), 1, 0, 63, 64, 65, 0, 0, 2, longest]
+    lens = np.concatenate([np.tile(near, 6), rng.integers(0, 40, 900), np.zeros(200, int),
+                           rng.integers(100, 129, 60), near])
+    lens = np.minimum(lens, longest)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    nc = 4096
+    col = (nc * rng.random(rp[-1]) ** 3).astype(np.int32)
+    vals = rng.uniform(-1, 1, rp[-1])
+    r, c, v = to_device(rp, col, vals, dtype, dev)
+    for validate in (True, False):
+        plan = pkg.Plan(r, c, v, nc, sigma=sigma, block_lanes=256, desc_bits=desc_bits,
+                        stripes=stripes, hot_columns=hot, validate=validate)
+        y = torch.full((len(rp) - 1,), float("nan"), dtype=dtype, device=dev)
+        z = torch.full_like(y, float("nan"))
+        for rep in range(2):
+            x64 = seeded_x(nc, 90 + rep, dtype)
+            x = torch.from_numpy(x64).to(dtype).to(dev)
+            plan.spmv(x, out=y)
+            torch.cuda.synchronize()
+            check_spmv(y, rp, col, host_values(vals, dtype), x64, dtype, f"call {rep}")
+        plan.zero_boundary(y)
+        plan.spmv_dual(x, y, z)
+        torch.cuda.synchronize()
+        check_spmv(y, rp, col, host_values(vals, dtype), x64, dtype, "dual 0")
+        if stripes == 0:
+            z[torch.isnan(z)] = 0.0  # rows the kernel did not have to zero
+            plan.spmv_dual(x, z, y)
+            torch.cuda.synchronize()
+            check_spmv(z, rp, col, host_values(vals, dtype), x64, dtype, "dual 1")
+        plan.close()
