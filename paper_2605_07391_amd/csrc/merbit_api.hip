@@ -675,11 +675,18 @@ int merbit_spmv(merbit_plan* p, const void* x, void* y, void* stream) try {
   hipStream_t st = static_cast<hipStream_t>(stream);
   // without long rows the wave kernel stores every row and y needs no zeros
   // (the longest row is known only of a validated plan)
+  bool hot_ready = false;
   if (p->row_start == nullptr || p->longest_row < 0 || p->longest_row > kOwnRowMax) {
-    const int rc = zero_boundary(p, y, st);
-    if (rc != MERBIT_OK) return rc;
+    if (p->stripes <= 1 && p->chunk_num > 0 && p->hot_n > 0 && !p->hot_all) {
+      HIP_TRY(launch_spmv_prologue(p->dtype, p->tile_y, (int32_t)p->chunk_num, p->unit_tiles, y, x,
+                                   p->hot_cols, p->hot_n, p->x_hot, st));
+      hot_ready = true;
+    } else {
+      const int rc = zero_boundary(p, y, st);
+      if (rc != MERBIT_OK) return rc;
+    }
   }
-  return run_fused(p, x, y, nullptr, st);
+  return run_fused(p, x, y, nullptr, st, hot_ready);
 } catch (...) {
   return merbit::host_exception();
 }

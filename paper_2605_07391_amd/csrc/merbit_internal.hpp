@@ -368,6 +368,10 @@ hipError_t launch_peek(const int32_t* src, const int64_t* idx, int n, int32_t* o
                        hipStream_t st);
 hipError_t launch_hot_gather(int dtype, const void* x, const int32_t* hot_cols, int32_t hot_n,
                              void* x_hot, hipStream_t st);
+// both in one launch: y zero at tile_y[k * unit] for k < units, and x_hot
+hipError_t launch_spmv_prologue(int dtype, const uint32_t* tile_y, int32_t units, int32_t unit,
+                                void* y, const void* x, const int32_t* hot_cols, int32_t hot_n,
+                                void* x_hot, hipStream_t st);
 // zero v at tile_y[k * unit] for k < units (the first row of every commit unit)
 hipError_t launch_zero_boundary(int dtype, const uint32_t* tile_y, int32_t units, int32_t unit,
                                 void* v, hipStream_t st);
