@@ -394,12 +394,12 @@ int merbit_bicgstab(merbit_plan* p, const void* b, void* x_inout, double tol, in
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t n = p->n_rows;
   if (!p->bvec[0]) {
-    for (int k = 0; k < 7; ++k) HIP_TRY(dev_alloc(&p->bvec[k], vsize(p->dtype) * (size_t)n));
+    for (int k = 0; k < 8; ++k) HIP_TRY(dev_alloc(&p->bvec[k], vsize(p->dtype) * (size_t)n));
     p->bicg_G = bicg_grid(n);
     for (int k = 0; k < 7; ++k)
       HIP_TRY(dev_alloc(&p->bpart[k], sizeof(double) * 2 * (size_t)p->bicg_G));
   }
-  // bvec: 0 r, 1 r^, 2 p, 3 v (even iterations), 4 v (odd), 5 s, 6 t
+  // bvec: 0 r, 1 r^, 2 p (even iterations), 3 v (even), 4 v (odd), 5 s, 6 t, 7 p (odd)
   // bpart: 0/1 (r^.r, r.r) by parity, 2/3 (r^.v, 0), 4/5 ((t,s), (t,t)), 6 (b.b, 0)
   BicgArgs a;
   memset(&a, 0, sizeof a);
@@ -409,9 +409,16 @@ int merbit_bicgstab(merbit_plan* p, const void* b, void* x_inout, double tol, in
   a.x = x_inout;
   a.r = p->bvec[0];
   a.rh = p->bvec[1];
-  a.p = p->bvec[2];
   a.s = p->bvec[5];
   a.t = p->bvec[6];
+  // with a partial hot-column cache the updates of p and s write the hot
+  // values of the SpMV that follows them
+  const bool fuse_hot = p->hot_n > 0 && !p->hot_all;
+  if (fuse_hot) {
+    a.hot_cols = p->hot_cols;
+    a.hot_n = p->hot_n;
+    a.x_hot = p->x_hot;
+  }
   // r_0 = b - A x_0 (t holds A x_0; the launch leaves v_even zero at the
   // boundary rows for iteration 0)
   int rc = zero_boundary(p, a.t, st);
@@ -458,13 +465,15 @@ int merbit_bicgstab(merbit_plan* p, const void* b, void* x_inout, double tol, in
         void* v_cur = p->bvec[3 + c];
         void* v_prev = p->bvec[3 + (c ^ 1)];
         q.v = v_prev;
+        q.p = p->bvec[c ? 7 : 2];
+        q.p_prev = p->bvec[c ? 2 : 7];
         HIP_TRY(launch_bicg(p->dtype, q, kBicgUpdateP, s));
-        int r = run_fused(p, q.p, v_cur, q.t, s);  // v = A p; clears t's boundary rows
+        int r = run_fused(p, q.p, v_cur, q.t, s, fuse_hot);  // v = A p; clears t's boundary rows
         if (r != MERBIT_OK) return r;
         q.v = v_cur;
         HIP_TRY(launch_bicg(p->dtype, q, kBicgDot1, s));
         HIP_TRY(launch_bicg(p->dtype, q, kBicgUpdateS, s));
-        r = run_fused(p, q.s, q.t, v_prev, s);  // t = A s; clears v_prev for it + 1
+        r = run_fused(p, q.s, q.t, v_prev, s, fuse_hot);  // t = A s; clears v_prev for it + 1
         if (r != MERBIT_OK) return r;
         HIP_TRY(launch_bicg(p->dtype, q, kBicgDot2, s));
         HIP_TRY(launch_bicg(p->dtype, q, kBicgUpdateXR, s));

@@ -91,8 +91,8 @@ struct merbit_plan {
   double* multi_gsum[2] = {nullptr, nullptr};
   int32_t* multi_hot_graph = nullptr;  // graph of each hot column slot
   int32_t multi_chunks = 0;
-  // BiCGSTAB state: r, r^, p, v (two), s, t; pair arrays of the dot products
-  void* bvec[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  // BiCGSTAB state: r, r^, p, v (two), s, t, p (second); pair arrays of the dot products
+  void* bvec[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   double* bpart[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   int bicg_G = 0;
   // HIP graphs of iteration chunks (the PageRank drivers); a graph holds the

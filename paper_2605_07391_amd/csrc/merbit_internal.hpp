@@ -433,6 +433,11 @@ struct BicgArgs {
   int first;   // iteration 0: p = r
   const void* b;
   void *x, *r, *rh, *p, *v, *s, *t;
+  const void* p_prev;  // update_p: p of the iteration before (another buffer than p)
+  // update_p and update_s also write the next SpMV's hot values (hot_n > 0)
+  const int32_t* hot_cols;
+  int32_t hot_n;
+  void* x_hot;
   const double *pa_cur, *pa_prev, *pb_prev, *pc_prev;
   double *pb_cur, *pc_cur, *pa_next, *pb_norm;
 };

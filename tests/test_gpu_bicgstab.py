@@ -205,3 +205,30 @@ def test_bicgstab_rmat21_benchmark_system(config):
     true_res = np.linalg.norm(b - oracle.spmv(rp, col, vals, x.cpu().numpy())) / np.linalg.norm(b)
     assert abs(true_res - res) <= 1e-6 * res + 1e-12, (true_res, res)
     plan.close()
+
+
+@pytest.mark.parametrize("stripes", [0, 8], ids=["plain", "striped8"])
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+@pytest.mark.parametrize("n", [1023, 1025, 3000])
+def test_partial_hot_cache(n, dtype, stripes):
+    """With a partial hot-column cache the updates of p and s write the hot
+    values of the SpMV that follows: calls of odd and even lengths, recorded
+    chunks and their replays, with the plan's own SpMV in between."""
+    dev = require_gpu()
+    rp, col, vals = _dominant(n, 9.0 / n, 2)
+    vals = vals.astype(_np(dtype)).astype(np.float64)
+    plan, keep = _plan(rp, col, vals, dtype, dev, commit="wave", hot_columns=60, stripes=stripes)
+    info = plan.info()
+    assert 0 < info["hot_columns"] and info["hot_coverage"] < 1.0
+    b = graphgen.uniform(2, 86, n, -1.0, 1.0).astype(_np(dtype)).astype(np.float64)
+    x0 = graphgen.uniform(2, 87, n, -1.0, 1.0).astype(_np(dtype)).astype(np.float64)
+    bt = torch.from_numpy(b).to(dtype).to(dev)
+    for k in (1, 4, 7, 6, 4):
+        x = torch.from_numpy(x0).to(dtype).to(dev)
+        it, _, status = plan.bicgstab(bt, x, tol=0.0, max_iter=k, check_every=3)
+        assert it == k and status == "done"
+        plan.spmv(bt)
+        ref = oracle.bicgstab(rp, col, vals, b, x0, 1e-300, k)[0]
+        err = np.abs(x.double().cpu().numpy() - ref).max() / np.abs(ref).max()
+        assert err <= ITER_TOL[dtype] * k, f"{k} iterations: {err:.3e}"
+    plan.close()
