@@ -251,12 +251,31 @@ __global__ __launch_bounds__(kReduceThreads) void adj_update_kernel(
   const V al = (V)alpha;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   double ssum = 0.0, rsum = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    V v = fma(al, y[i], g[i]);
-    if ((dmask[i >> 5] >> (i & 31)) & 1u) v += dang;
-    lam_new[i] = v;
-    ssum += (double)v;
-    rsum += fabs((double)v - (double)lam_old[i]);
+  // kAdjILP elements per thread in flight (one: 9.4 us on R-MAT 20 FP32, four: 7.8)
+  constexpr int kAdjILP = 4;
+  for (int64_t base = (int64_t)blockIdx.x * blockDim.x * kAdjILP + threadIdx.x; base < n;
+       base += stride * kAdjILP) {
+    V yv[kAdjILP], gv[kAdjILP], lo[kAdjILP];
+    uint32_t mw[kAdjILP];
+#pragma unroll
+    for (int u = 0; u < kAdjILP; ++u) {
+      const int64_t i = min(base + (int64_t)u * kReduceThreads, n - 1);
+      yv[u] = y[i];
+      gv[u] = g[i];
+      lo[u] = lam_old[i];
+      mw[u] = dmask[i >> 5];
+    }
+#pragma unroll
+    for (int u = 0; u < kAdjILP; ++u) {
+      const int64_t i = base + (int64_t)u * kReduceThreads;
+      if (i < n) {
+        V v = fma(al, yv[u], gv[u]);
+        if ((mw[u] >> (i & 31)) & 1u) v += dang;
+        lam_new[i] = v;
+        ssum += (double)v;
+        rsum += fabs((double)v - (double)lo[u]);
+      }
+    }
   }
   for (int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; h < hot_n; h += stride) {
     const int64_t c = hot_cols[h];
