@@ -350,8 +350,11 @@ hipError_t launch_spmm_zero(int dtype, const uint32_t* tile_y, int32_t tile_num,
 // and clears those slots of Y for the next step; on the last step of a
 // chunk ppr_resid_kernel adds the l1 change.  A last kernel (one block per
 // column) sums the parts in a fixed order for the next step and the host.
-// Thread t of these kernels always handles column t % 64, so each
-// wavefront reads and writes whole rows (coalesced).
+// Thread t of the part kernels always handles column t % K, K the power of two
+// from k on, so each wavefront reads and writes 64 / K whole rows (coalesced;
+// with column t % 64 the dangling, l1 and fixup kernels took 17.8, 13.4 and
+// 8.2 us on R-MAT 18 FP32, k = 16, with 64 / K rows a wavefront 6.7, 7.1 and
+// 4.9).
 //
 // The iterates (and A X) are held as slabs of kSlab columns one after
 // another: slab s is the row-major n x W_s block of columns 32 s .. 32 s +
@@ -371,10 +374,19 @@ constexpr int kPprThreads = 256;
 constexpr int kPprWaves = kPprThreads / 64;
 constexpr int kPprRows = 4;
 
-// 64 per-thread (a, b) pairs of the block (thread t: column t % 64) summed
-// over its wavefronts in order, written as part_out row blockIdx.x
-__device__ __forceinline__ void ppr_block_part(double a, double b, double* __restrict__ part_out) {
+// log2 of the columns K that a part kernel's lanes span
+__device__ __forceinline__ int ppr_log_cols(int k) { return k > 1 ? 32 - __builtin_clz(k - 1) : 0; }
+
+// per-thread (a, b) pairs of the block (thread t: column t % 2^ks) summed over
+// each wavefront's rows in a fixed tree, then over the wavefronts in order, and
+// written as part_out row blockIdx.x
+__device__ __forceinline__ void ppr_block_part(double a, double b, double* __restrict__ part_out,
+                                               int ks = 6) {
   __shared__ double s_a[kPprThreads], s_b[kPprThreads];
+  for (int off = 32; off >= (1 << ks); off >>= 1) {
+    a += __shfl_xor(a, off, kOmega);
+    b += __shfl_xor(b, off, kOmega);
+  }
   s_a[threadIdx.x] = a;
   s_b[threadIdx.x] = b;
   __syncthreads();
@@ -402,15 +414,16 @@ __global__ __launch_bounds__(kPprThreads) void ppr_fixup_kernel(
     V* __restrict__ Xn, int64_t n, int k, double alpha, const int32_t* __restrict__ src,
     const double* __restrict__ sums_in, const uint32_t* __restrict__ dmask,
     double* __restrict__ part_out) {
-  const int j = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
+  const int ks = ppr_log_cols(k);
+  const int j = threadIdx.x & ((1 << ks) - 1);
+  const int w = threadIdx.x >> ks;
   const bool on = j < k;
   const int sj = on ? src[j] : -1;
   const V a = (V)alpha;
   const V tele = on ? (V)(alpha * sums_in[2 * j] + 1.0 - alpha) : V(0);
   double dsum = 0.0;
-  const int64_t step = (int64_t)gridDim.x * kPprWaves;
-  for (int64_t t = (int64_t)blockIdx.x * kPprWaves + w; t < tile_num; t += step) {
+  const int64_t step = (int64_t)gridDim.x * (kPprThreads >> ks);
+  for (int64_t t = (int64_t)blockIdx.x * (kPprThreads >> ks) + w; t < tile_num; t += step) {
     const int64_t r = tile_y[t] & kRowMask;
     // each first row once (a long row is the first row of several tiles)
     if (r >= n || (t > 0 && (int64_t)(tile_y[t - 1] & kRowMask) == r)) continue;
@@ -423,7 +436,7 @@ __global__ __launch_bounds__(kPprThreads) void ppr_fixup_kernel(
       if ((dmask[r >> 5] >> (r & 31)) & 1u) dsum += (double)xn;
     }
   }
-  ppr_block_part(dsum, 0.0, part_out);
+  ppr_block_part(dsum, 0.0, part_out, ks);
 }
 
 template <typename V>
@@ -431,24 +444,25 @@ __global__ __launch_bounds__(kPprThreads) void ppr_resid_kernel(const V* __restr
                                                                 const V* __restrict__ Xo,
                                                                 int64_t n, int k,
                                                                 double* __restrict__ part_out) {
-  const int j = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
+  const int ks = ppr_log_cols(k);
+  const int j = threadIdx.x & ((1 << ks) - 1);
+  const int rb = kPprThreads >> ks;  // rows per pass of the block
   double rsum = 0.0;
-  const int64_t step = (int64_t)gridDim.x * kPprWaves * kPprRows;
-  for (int64_t r0 = ((int64_t)blockIdx.x * kPprWaves + w) * kPprRows; j < k && r0 < n;
+  const int64_t step = (int64_t)gridDim.x * rb * kPprRows;
+  for (int64_t r0 = (int64_t)blockIdx.x * rb * kPprRows + (threadIdx.x >> ks); j < k && r0 < n;
        r0 += step) {
     V xn[kPprRows], xo[kPprRows];
 #pragma unroll
     for (int u = 0; u < kPprRows; ++u) {
-      const int64_t e = ppr_at(min(r0 + u, n - 1), j, n, k);
+      const int64_t e = ppr_at(min(r0 + u * rb, n - 1), j, n, k);
       xn[u] = Xn[e];
       xo[u] = Xo[e];
     }
 #pragma unroll
     for (int u = 0; u < kPprRows; ++u)
-      if (r0 + u < n) rsum += fabs((double)xn[u] - (double)xo[u]);
+      if (r0 + u * rb < n) rsum += fabs((double)xn[u] - (double)xo[u]);
   }
-  ppr_block_part(0.0, rsum, part_out);
+  ppr_block_part(0.0, rsum, part_out, ks);
 }
 
 // dangling mass of X (per column) -> the same per-block part layout
@@ -456,19 +470,28 @@ template <typename V>
 __global__ __launch_bounds__(kPprThreads) void ppr_dangling_kernel(
     const V* __restrict__ X, const uint32_t* __restrict__ dmask, int64_t n, int k,
     double* __restrict__ part_out) {
-  const int j = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
+  const int ks = ppr_log_cols(k);
+  const int j = threadIdx.x & ((1 << ks) - 1);
+  const int rb = kPprThreads >> ks;  // rows per pass of the block
   double dsum = 0.0;
-  const int64_t step = (int64_t)gridDim.x * kPprWaves * kPprRows;
-  for (int64_t r0 = ((int64_t)blockIdx.x * kPprWaves + w) * kPprRows; j < k && r0 < n;
+  const int64_t step = (int64_t)gridDim.x * rb * kPprRows;
+  for (int64_t r0 = (int64_t)blockIdx.x * rb * kPprRows + (threadIdx.x >> ks); j < k && r0 < n;
        r0 += step) {
+    V v[kPprRows];
+    uint32_t mw[kPprRows];
 #pragma unroll
     for (int u = 0; u < kPprRows; ++u) {
-      const int64_t r = r0 + u;
-      if (r < n && ((dmask[r >> 5] >> (r & 31)) & 1u)) dsum += (double)X[ppr_at(r, j, n, k)];
+      const int64_t r = min(r0 + u * rb, n - 1);
+      v[u] = X[ppr_at(r, j, n, k)];
+      mw[u] = dmask[r >> 5];
+    }
+#pragma unroll
+    for (int u = 0; u < kPprRows; ++u) {
+      const int64_t r = r0 + u * rb;
+      if (r < n && ((mw[u] >> (r & 31)) & 1u)) dsum += (double)v[u];
     }
   }
-  ppr_block_part(dsum, 0.0, part_out);
+  ppr_block_part(dsum, 0.0, part_out, ks);
 }
 
 // the slab layout back into the caller's row-major n x k (ld k), one
@@ -531,9 +554,20 @@ __global__ __launch_bounds__(kReduceThreads) void ppr_sum_parts_kernel(
     const double* __restrict__ part, int nblocks, double* __restrict__ sums) {
   const int j = blockIdx.x;
   double d = 0.0, r = 0.0;
-  for (int b = threadIdx.x; b < nblocks; b += kReduceThreads) {
-    d += part[((int64_t)b * 64 + j) * 2];
-    r += part[((int64_t)b * 64 + j) * 2 + 1];
+  const double2* __restrict__ p2 = reinterpret_cast<const double2*>(part);
+  constexpr int kPartILP = 8;  // loads in flight per thread
+  for (int b = threadIdx.x; b < nblocks; b += kPartILP * kReduceThreads) {
+    double2 v[kPartILP];
+#pragma unroll
+    for (int u = 0; u < kPartILP; ++u)
+      v[u] = p2[(int64_t)min(b + u * kReduceThreads, nblocks - 1) * 64 + j];
+#pragma unroll
+    for (int u = 0; u < kPartILP; ++u) {
+      if (b + u * kReduceThreads < nblocks) {
+        d += v[u].x;
+        r += v[u].y;
+      }
+    }
   }
   block_sum2(d, r);
   if (threadIdx.x == 0) {

@@ -502,3 +502,25 @@ def test_batched_graph_replays_match_eager():
         assert d <= 2 * PR_TOL[torch.float64], f"multi replay {rep}: {d:.3e}"
     g_plan.close()
     e_plan.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+@pytest.mark.parametrize("k", [2, 3, 8, 9, 16, 31, 32])
+def test_personalized_pagerank_lanes_of_several_rows(k, dtype):
+    """Widths around the powers of two that set how many rows a wavefront of
+    the part kernels takes, on row counts around a block's pass, entry by
+    entry against the oracle."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    for n, density in ((3, 0.6), (63, 0.1), (257, 0.02), (1025, 0.006)):
+        rp, col, _ = graphgen.random_csr(n, n, density, seed=n, empty_frac=0.2)
+        vals = graphgen.column_stochastic_values(col, n)
+        r, c, v = to_device(rp, col, vals, dtype, dev)
+        plan = pkg.Plan(r, c, v, n)
+        src = ((np.arange(k) * 5 + 1) % n).astype(np.int32)
+        X, iters, _, _ = plan.pagerank_personalized(src, alpha=ALPHA, max_iter=9, check_every=4)
+        torch.cuda.synchronize()
+        ref = oracle.personalized_pagerank(rp, col, host_values(vals, dtype), ALPHA, 9, src)
+        assert iters == 9
+        _ppr_check(X, ref, dtype, f"n={n} k={k}")
+        plan.close()
