@@ -169,7 +169,7 @@ static int ensure_multi_tables(merbit_plan* p, const int64_t* graph_ptr, int n_g
   HIP_TRY(dev_alloc(&p->multi_chunk_graph, sizeof(int32_t) * C));
   HIP_TRY(dev_alloc(&p->multi_chunk_ptr, sizeof(int32_t) * (size_t)(n_graphs + 1)));
   HIP_TRY(dev_alloc(&p->multi_gsize, sizeof(double) * (size_t)n_graphs));
-  HIP_TRY(dev_alloc(&p->multi_part, sizeof(double) * 2 * C));
+  HIP_TRY(dev_alloc(&p->multi_part, sizeof(double) * 4 * C));
   HIP_TRY(dev_alloc(&p->multi_gsum[0], sizeof(double) * 2 * (size_t)n_graphs));
   HIP_TRY(dev_alloc(&p->multi_gsum[1], sizeof(double) * 2 * (size_t)n_graphs));
   HIP_TRY(hipMemcpy(p->multi_chunk_row, chunk_row.data(), sizeof(int32_t) * (C + 1),
@@ -186,6 +186,9 @@ static int ensure_multi_tables(merbit_plan* p, const int64_t* graph_ptr, int n_g
                       hipMemcpyHostToDevice));
   }
   p->multi_chunks = (int32_t)C;
+  p->multi_max_chunks = 0;
+  for (int g = 0; g < n_graphs; ++g)
+    p->multi_max_chunks = std::max(p->multi_max_chunks, chunk_ptr[g + 1] - chunk_ptr[g]);
   p->multi_gp = gp;
   return MERBIT_OK;
 }
@@ -219,7 +222,9 @@ int merbit_pagerank_multi(merbit_plan* p, const int64_t* graph_ptr, int n_graphs
   mt.chunk_graph = p->multi_chunk_graph;
   mt.chunk_ptr = p->multi_chunk_ptr;
   mt.gsize = p->multi_gsize;
-  mt.part = p->multi_part;
+  mt.part[0] = p->multi_part;
+  mt.part[1] = p->multi_part + 2 * (size_t)p->multi_chunks;
+  mt.max_chunks = p->multi_max_chunks;
   mt.hot_graph = p->multi_hot_graph;
   mt.n_chunks = p->multi_chunks;
   mt.n_graphs = n_graphs;
@@ -250,7 +255,7 @@ int merbit_pagerank_multi(merbit_plan* p, const int64_t* graph_ptr, int n_graphs
                                 fuse_hot && t0 + i > 0);
         if (r != MERBIT_OK) return r;
         HIP_TRY(launch_multi_update(p->dtype, p->ybuf[b], xs[cur], xs[cur ^ 1], p->dmask, mt,
-                                    alpha, p->multi_gsum[cur], p->multi_gsum[cur ^ 1], s,
+                                    alpha, cur, p->multi_gsum[cur], p->multi_gsum[cur ^ 1], s,
                                     fuse_hot ? p->hot_cols : nullptr, fuse_hot ? p->hot_n : 0,
                                     fuse_hot ? p->x_hot : nullptr, i == len - 1));
       }

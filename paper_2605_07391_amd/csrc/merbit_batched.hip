@@ -686,31 +686,66 @@ hipError_t launch_ppr_resid(int dtype, const void* Xn, const void* Xo, int64_t n
 // Rows are cut into chunks of at most kMultiRows rows that never cross a
 // graph; chunk c is rows [chunk_row[c], chunk_row[c+1]) of graph
 // chunk_graph[c], and graph g's chunks are chunk_ptr[g] .. chunk_ptr[g+1]-1.
-// One block per chunk writes the chunk's (dangling mass, l1 change) pair; a
-// second kernel adds each graph's pairs in chunk order (deterministic).
+// One block per chunk writes the chunk's (dangling mass, l1 change) pair.  A
+// graph's pairs are added in chunk order (deterministic) by the next update's
+// wavefronts, each for itself, or by a second kernel: after the step whose
+// sums the host reads, and after every step where a graph has more than
+// kMultiFoldChunks chunks or the update writes hot values (a hot column's
+// graph is another than its block's).  Microseconds per iteration with the
+// second kernel and without, FP32, 8 edges per row: 64 graphs of 10,000 rows
+// 33.8 and 31.8; one graph of 489 chunks 30.2 and 29.0, of 977 49.9 and 49.3,
+// of 1,954 77.4 and 79.9 (every wavefront reads all the pairs).
 
 constexpr int kMultiILP = 4;
 constexpr int kMultiRows = kReduceThreads * kMultiILP;
 
 int multi_chunk_rows() { return kMultiRows; }
 
+constexpr int kMultiFoldChunks = 512;
+
+// (dangling mass, l1 change) of the chunks c0 .. c1 - 1, in every lane: lane l
+// adds chunks c0 + l, c0 + l + 64, ... in order, then a fixed-order wavefront
+// reduction
+__device__ __forceinline__ double2 multi_graph_sum(const double* __restrict__ part, int c0, int c1,
+                                                   int lid) {
+  constexpr int kILP = 4;  // loads in flight per lane
+  const double2* __restrict__ p2 = reinterpret_cast<const double2*>(part);
+  double2 s = {0.0, 0.0};
+  for (int c = c0 + lid; c < c1; c += kILP * kOmega) {
+    double2 v[kILP];
+#pragma unroll
+    for (int u = 0; u < kILP; ++u) v[u] = p2[min(c + u * kOmega, c1 - 1)];
+#pragma unroll
+    for (int u = 0; u < kILP; ++u) {
+      if (c + u * kOmega < c1) {
+        s.x += v[u].x;
+        s.y += v[u].y;
+      }
+    }
+  }
+  s.x = wave_sum(s.x);
+  s.y = wave_sum(s.y);
+  return s;
+}
+
 // With hot_n > 0 the kernel also writes the hot-column copy of x' that the
 // next SpMV's LDS cache reads: slot s holds column hot_cols[s] of graph
 // hot_graph[s], computed with the same operations as that row's x'.
 // Without RESID x_old is not read and the l1 parts are 0 (the host reads
-// the l1 change only after a chunk's last step).
+// the l1 change only after a chunk's last step).  part_in: the step before's
+// pairs, added here instead of read from gsum_in (without hot columns).
 template <typename V, bool RESID>
 __global__ __launch_bounds__(kReduceThreads) void multi_update_kernel(
     const V* __restrict__ y, const V* __restrict__ x_old, V* __restrict__ x_new,
     const uint32_t* __restrict__ dmask, const int32_t* __restrict__ chunk_row,
-    const int32_t* __restrict__ chunk_graph, const double* __restrict__ gsum_in,
+    const int32_t* __restrict__ chunk_graph, const int32_t* __restrict__ chunk_ptr,
+    const double* __restrict__ gsum_in, const double* __restrict__ part_in,
     const double* __restrict__ gsize, double alpha, double* __restrict__ part_out,
     const int32_t* __restrict__ hot_cols, const int32_t* __restrict__ hot_graph, int32_t hot_n,
     V* __restrict__ x_hot) {
   const int c = blockIdx.x;
   const int64_t r0 = chunk_row[c], r1 = chunk_row[c + 1];
   const int g = chunk_graph[c];
-  const V tele = (V)((alpha * gsum_in[2 * g] + 1.0 - alpha) / gsize[g]);
   const V a = (V)alpha;
   V yv[kMultiILP], xo[kMultiILP];
   uint32_t mw[kMultiILP];
@@ -721,6 +756,11 @@ __global__ __launch_bounds__(kReduceThreads) void multi_update_kernel(
     if constexpr (RESID) xo[u] = x_old[i];
     mw[u] = dmask[i >> 5];
   }
+  const double delta = part_in != nullptr
+                           ? multi_graph_sum(part_in, chunk_ptr[g], chunk_ptr[g + 1],
+                                             threadIdx.x & (kOmega - 1)).x
+                           : gsum_in[2 * g];
+  const V tele = (V)((alpha * delta + 1.0 - alpha) / gsize[g]);
   double dsum = 0.0, rsum = 0.0;
 #pragma unroll
   for (int u = 0; u < kMultiILP; ++u) {
@@ -761,8 +801,7 @@ __global__ __launch_bounds__(kReduceThreads) void multi_dangling_kernel(
   }
 }
 
-// One wavefront per graph: lane l adds chunks chunk_ptr[g] + l, + l + 64, ...
-// in order, then a fixed-order wavefront reduction.
+// one wavefront per graph
 __global__ __launch_bounds__(256) void multi_sum_kernel(const double* __restrict__ part,
                                                          const int32_t* __restrict__ chunk_ptr,
                                                          int n_graphs,
@@ -770,16 +809,10 @@ __global__ __launch_bounds__(256) void multi_sum_kernel(const double* __restrict
   const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lid = threadIdx.x & 63;
   if (g >= n_graphs) return;
-  double d = 0.0, r = 0.0;
-  for (int c = chunk_ptr[g] + lid; c < chunk_ptr[g + 1]; c += 64) {
-    d += part[2 * c];
-    r += part[2 * c + 1];
-  }
-  d = wave_sum(d);
-  r = wave_sum(r);
+  const double2 s = multi_graph_sum(part, chunk_ptr[g], chunk_ptr[g + 1], lid);
   if (lid == 0) {
-    gsum_out[2 * g] = d;
-    gsum_out[2 * g + 1] = r;
+    gsum_out[2 * g] = s.x;
+    gsum_out[2 * g + 1] = s.y;
   }
 }
 
@@ -795,21 +828,23 @@ hipError_t launch_multi_dangling(int dtype, const void* x, const uint32_t* dmask
   if (dtype == 0)
     hipLaunchKernelGGL(multi_dangling_kernel<float>, dim3((unsigned)mt.n_chunks),
                        dim3(kReduceThreads), 0, st, static_cast<const float*>(x), dmask,
-                       mt.chunk_row, mt.part);
+                       mt.chunk_row, mt.part[0]);
   else
     hipLaunchKernelGGL(multi_dangling_kernel<double>, dim3((unsigned)mt.n_chunks),
                        dim3(kReduceThreads), 0, st, static_cast<const double*>(x), dmask,
-                       mt.chunk_row, mt.part);
+                       mt.chunk_row, mt.part[0]);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_multi_sum(mt.part, mt.chunk_ptr, mt.n_graphs, gsum_out, st);
+  return launch_multi_sum(mt.part[0], mt.chunk_ptr, mt.n_graphs, gsum_out, st);
 }
 
 template <typename V>
 static void multi_update_launch(bool resid, const void* y, const void* x_old, void* x_new,
                                 const uint32_t* dmask, const MultiTables& mt, double alpha,
-                                const double* gsum_in, hipStream_t st, const int32_t* hot_cols,
-                                int32_t hot_n, void* x_hot) {
+                                int cur, const double* gsum_in, bool fold, hipStream_t st,
+                                const int32_t* hot_cols, int32_t hot_n, void* x_hot) {
+  const double* part_in = fold ? mt.part[cur] : nullptr;
+  double* part_out = mt.part[cur ^ 1];
   const V* yv = static_cast<const V*>(y);
   const V* xo = static_cast<const V*>(x_old);
   V* xn = static_cast<V*>(x_new);
@@ -817,29 +852,31 @@ static void multi_update_launch(bool resid, const void* y, const void* x_old, vo
   if (resid)
     hipLaunchKernelGGL((multi_update_kernel<V, true>), dim3((unsigned)mt.n_chunks),
                        dim3(kReduceThreads), 0, st, yv, xo, xn, dmask, mt.chunk_row,
-                       mt.chunk_graph, gsum_in, mt.gsize, alpha, mt.part, hot_cols,
-                       mt.hot_graph, hot_n, xh);
+                       mt.chunk_graph, mt.chunk_ptr, gsum_in, part_in, mt.gsize, alpha, part_out,
+                       hot_cols, mt.hot_graph, hot_n, xh);
   else
     hipLaunchKernelGGL((multi_update_kernel<V, false>), dim3((unsigned)mt.n_chunks),
                        dim3(kReduceThreads), 0, st, yv, xo, xn, dmask, mt.chunk_row,
-                       mt.chunk_graph, gsum_in, mt.gsize, alpha, mt.part, hot_cols,
-                       mt.hot_graph, hot_n, xh);
+                       mt.chunk_graph, mt.chunk_ptr, gsum_in, part_in, mt.gsize, alpha, part_out,
+                       hot_cols, mt.hot_graph, hot_n, xh);
 }
 
 hipError_t launch_multi_update(int dtype, const void* y, const void* x_old, void* x_new,
                                const uint32_t* dmask, const MultiTables& mt, double alpha,
-                               const double* gsum_in, double* gsum_out, hipStream_t st,
-                               const int32_t* hot_cols, int32_t hot_n, void* x_hot, bool resid) {
+                               int cur, const double* gsum_in, double* gsum_out,
+                               hipStream_t st, const int32_t* hot_cols, int32_t hot_n,
+                               void* x_hot, bool resid) {
   if (hot_n > 0 && mt.hot_graph == nullptr) return hipErrorInvalidValue;
+  const bool fold = hot_n == 0 && mt.max_chunks <= kMultiFoldChunks;
   if (dtype == 0)
-    multi_update_launch<float>(resid, y, x_old, x_new, dmask, mt, alpha, gsum_in, st, hot_cols,
-                               hot_n, x_hot);
+    multi_update_launch<float>(resid, y, x_old, x_new, dmask, mt, alpha, cur, gsum_in, fold, st,
+                               hot_cols, hot_n, x_hot);
   else
-    multi_update_launch<double>(resid, y, x_old, x_new, dmask, mt, alpha, gsum_in, st, hot_cols,
-                                hot_n, x_hot);
+    multi_update_launch<double>(resid, y, x_old, x_new, dmask, mt, alpha, cur, gsum_in, fold, st,
+                                hot_cols, hot_n, x_hot);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_multi_sum(mt.part, mt.chunk_ptr, mt.n_graphs, gsum_out, st);
+  if (e != hipSuccess || (fold && !resid)) return e;
+  return launch_multi_sum(mt.part[cur ^ 1], mt.chunk_ptr, mt.n_graphs, gsum_out, st);
 }
 
 }  // namespace merbit

@@ -87,10 +87,11 @@ struct merbit_plan {
   int32_t* multi_chunk_graph = nullptr;
   int32_t* multi_chunk_ptr = nullptr;
   double* multi_gsize = nullptr;
-  double* multi_part = nullptr;
+  double* multi_part = nullptr;  // two arrays of pairs
   double* multi_gsum[2] = {nullptr, nullptr};
   int32_t* multi_hot_graph = nullptr;  // graph of each hot column slot
   int32_t multi_chunks = 0;
+  int32_t multi_max_chunks = 0;  // of one graph
   // BiCGSTAB state: r, r^, p, v (two), s, t, p (second); pair arrays of the dot products
   void* bvec[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   double* bpart[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};

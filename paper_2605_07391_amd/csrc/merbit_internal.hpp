@@ -504,20 +504,24 @@ struct MultiTables {  // device row-chunk tables of a block-diagonal matrix
   const int32_t* chunk_graph;  // [n_chunks]
   const int32_t* chunk_ptr;    // [n_graphs + 1]
   const double* gsize;         // [n_graphs] vertex count of each graph
-  double* part;                // [2 n_chunks] per-chunk pairs
+  double* part[2];             // [2 n_chunks] each: per-chunk pairs before even and odd steps
   const int32_t* hot_graph;    // [hot_n] graph of each hot column slot (or null)
   int32_t n_chunks;
   int32_t n_graphs;
+  int32_t max_chunks;          // of one graph
 };
 int multi_chunk_rows();
 hipError_t launch_multi_dangling(int dtype, const void* x, const uint32_t* dmask,
                                  const MultiTables& mt, double* gsum_out, hipStream_t st);
 // hot_n > 0 (needs mt.hot_graph): also the next SpMV's hot-column copy of x'
-// resid: also the per-graph l1 change (second components of gsum_out; else 0)
+// resid: also the per-graph l1 change (second components of gsum_out; else 0).
+// Step `cur` (0 even, 1 odd) reads part[cur] or gsum_in and writes
+// part[cur ^ 1]; gsum_out is left as it is where the next step reads part and
+// resid is not asked for.
 hipError_t launch_multi_update(int dtype, const void* y, const void* x_old, void* x_new,
                                const uint32_t* dmask, const MultiTables& mt, double alpha,
-                               const double* gsum_in, double* gsum_out, hipStream_t st,
-                               const int32_t* hot_cols = nullptr, int32_t hot_n = 0,
+                               int cur, const double* gsum_in, double* gsum_out,
+                               hipStream_t st, const int32_t* hot_cols = nullptr, int32_t hot_n = 0,
                                void* x_hot = nullptr, bool resid = true);
 hipError_t launch_spmm(int dtype, int sigma, const SpmmArgs& a, hipStream_t st);
 hipError_t launch_spmm_zero(int dtype, const uint32_t* tile_y, int32_t tile_num, void* Y,

@@ -524,3 +524,40 @@ def test_personalized_pagerank_lanes_of_several_rows(k, dtype):
         assert iters == 9
         _ppr_check(X, ref, dtype, f"n={n} k={k}")
         plan.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+@pytest.mark.parametrize("rows", [65 * 1024, 512 * 1024, 512 * 1024 + 1])
+def test_pagerank_multi_chunk_sums(rows, dtype):
+    """Graphs of 65, 512 and 513 chunks of 1,024 rows beside a small one: the
+    update adds a graph's chunk pairs itself up to 512 of them, more than one
+    round of a wavefront; odd lengths and recorded chunks of 3 steps."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    gp = np.array([0, 700, 700 + rows], dtype=np.int64)
+    n = int(gp[-1])
+    # a ring with a chord inside each graph, every fifth vertex dangling
+    r = np.arange(n, dtype=np.int64)
+    lo = np.where(r < 700, 0, 700)
+    size = np.where(r < 700, 700, rows)
+    col = np.stack([lo + (r - lo + 1) % size, lo + (r - lo + 7) % size], 1)
+    col.sort(axis=1)
+    keep = col % 5 != 0
+    rp = np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int32)
+    col = col[keep].astype(np.int32)
+    vals = graphgen.column_stochastic_values(col, n)
+    rt, ct, vt = to_device(rp, col, vals, dtype, dev)
+    plan = pkg.Plan(rt, ct, vt, n, hot_columns=0)
+    x064 = _multi_x0(gp, dtype)
+    ref = {}
+    for iters in (7, 6, 7):
+        x = torch.from_numpy(x064).to(dtype).to(dev)
+        it, resid, _ = plan.pagerank_multi(gp, x, alpha=ALPHA, max_iter=iters, check_every=3)
+        torch.cuda.synchronize()
+        assert it == iters and np.all(np.isfinite(resid))
+        if iters not in ref:
+            ref[iters] = oracle.pagerank_multi(rp, col, host_values(vals, dtype), gp, ALPHA,
+                                               iters, x064)
+        rel = np.abs(x.double().cpu().numpy() - ref[iters]) / ref[iters]
+        assert rel.max() <= PR_TOL[dtype], rel.max()
+    plan.close()
