@@ -372,7 +372,7 @@ def run_ppr(w, k: int, steps: int, warmup: int, alpha: float, sigma: int = 0):
                          # the SpMM of the step, fused with the update of the
                          # rows inside tiles: one launch per 32-column slab
                          # (128 bytes of X row), timed together
-                         "kernel": "merbit::spmm_kernel<float, 32, true>",
+                         "kernel": "merbit::spmm_kernel<float, 8, 4, true>",
                          "launches_per_spmm": -(-k // 32),
                          "alg_bytes_per_spmm": int(alg),
                          "mean_spmm_us": round(spmm_ms * 1e3, 1)}}
