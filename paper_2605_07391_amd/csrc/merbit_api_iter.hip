@@ -398,12 +398,12 @@ int merbit_bicgstab(merbit_plan* p, const void* b, void* x_inout, double tol, in
   if (check_every <= 0) check_every = 10;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t n = p->n_rows;
-  if (!p->bvec[0]) {
-    for (int k = 0; k < 8; ++k) HIP_TRY(dev_alloc(&p->bvec[k], vsize(p->dtype) * (size_t)n));
-    p->bicg_G = bicg_grid(n);
-    for (int k = 0; k < 7; ++k)
-      HIP_TRY(dev_alloc(&p->bpart[k], sizeof(double) * 2 * (size_t)p->bicg_G));
-  }
+  // (an earlier call may have run out of memory after some of them)
+  p->bicg_G = bicg_grid(n);
+  for (void*& v : p->bvec)
+    if (!v) HIP_TRY(dev_alloc(&v, vsize(p->dtype) * (size_t)n));
+  for (double*& v : p->bpart)
+    if (!v) HIP_TRY(dev_alloc(&v, sizeof(double) * 2 * (size_t)p->bicg_G));
   // bvec: 0 r, 1 r^, 2 p (even iterations), 3 v (even), 4 v (odd), 5 s, 6 t, 7 p (odd)
   // bpart: 0/1 (r^.r, r.r) by parity, 2/3 (r^.v, 0), 4/5 ((t,s), (t,t)), 6 (b.b, 0)
   BicgArgs a;
