@@ -288,7 +288,7 @@ int64_t hot_cap_lds(const merbit_plan* p) {
   return (cap / 256) * 256;
 }
 
-constexpr int64_t kHotMinTilesPerWave = 4;
+constexpr int64_t kHotMinStepsPerCu = 15360;
 
 static int build_hot_cache(merbit_plan* p, int cap_req, hipStream_t st) {
   p->hot_n = 0;
@@ -298,14 +298,17 @@ static int build_hot_cache(merbit_plan* p, int cap_req, hipStream_t st) {
   // every wavefront of a block wait for the slowest, which measured slower
   // than no cache at every size (R-MAT 22).  An explicit size is honoured.
   if (cap_req < 0 && p->commit != MERBIT_COMMIT_WAVE) return MERBIT_OK;
-  // Nor for a plan too small to amortise the fill: with fewer than
-  // kHotMinTilesPerWave tiles per wavefront of one block per CU, each block
-  // copies x into LDS for about one tile of work (the 10,000-vertex
-  // Chung-Lu matrix: 7.3 instead of 8.9 us per SpMV without the cache).
+  // Nor for a plan too small to amortise the fill and the launch before the
+  // kernel: below 15,360 merge-path steps per CU (3.9M in all).  SpMV without
+  // and with the cache, default blocks, FP32: R-MAT 17 (2.1M steps) 12.2 and
+  // 12.5 us, Chung-Lu 300,000 x 8 (2.3M) 10.6 and 14.7, R-MAT 18 (4.2M) 23.4
+  // and 18.4, Chung-Lu 700,001 x 6 (4.3M) 21.2 and 20.4, R-MAT 19 (8.4M) 41.9
+  // and 30.6; FP64: R-MAT 17 16.0 and 16.3, R-MAT 18 29.9 and 24.9, Chung-Lu
+  // 300,000 x 16 (4.4M) 26.2 and 27.9, an iteration of PageRank 35.6 and 35.6.
   if (cap_req < 0) {
     int cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    if (p->tile_num < (int64_t)kHotMinTilesPerWave * cus * p->waves) return MERBIT_OK;
+    if (p->nnz + p->plan_rows < kHotMinStepsPerCu * cus) return MERBIT_OK;
   }
   if (!kernel_supported(p, true))
     return cap_req > 0 ? fail(MERBIT_EUNSUPPORTED, "hot cache not built for this block size")

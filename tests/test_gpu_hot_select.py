@@ -166,3 +166,36 @@ def test_wide_sparse_matrix_hot_set(stripes):
     torch.cuda.synchronize()
     check_spmv(y, rp, col, host_values(vals, torch.float32), x64, torch.float32, "wide sparse")
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64], ids=["f32", "f64"])
+@pytest.mark.parametrize("steps", [-1, 0], ids=["below", "at"])
+def test_automatic_cache_threshold(steps, dtype):
+    """A default plan has a hot-column cache from 15,360 merge-path steps per
+    CU on; y on both sides of the line against float64 sums, within 1e-5 /
+    1e-12 of |A||x| per row."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 150_000
+    nnz = 15360 * cus - n + steps
+    rng = np.random.default_rng(15)
+    row_ptr = np.sort(np.concatenate([[0, nnz], rng.integers(0, nnz + 1, n - 1)]))
+    # six of ten nonzeros in 2,000 columns, so that the cache is worth keeping
+    col = np.where(rng.random(nnz) < 0.6, rng.integers(0, 2000, nnz), rng.integers(0, n, nnz))
+    vals = rng.uniform(0.5, 1.5, nnz)
+    x = rng.uniform(0.5, 1.5, n)
+    r = torch.from_numpy(row_ptr.astype(np.int32)).to(dev)
+    c = torch.from_numpy(col.astype(np.int32)).to(dev)
+    v = torch.from_numpy(vals).to(dtype).to(dev)
+    xt = torch.from_numpy(x).to(dtype).to(dev)
+    plan = pkg.Plan(r, c, v, n)
+    assert (plan.info()["hot_columns"] > 0) == (steps == 0)
+    y = plan.spmv(xt).double().cpu().numpy()
+    prod = v.double().cpu().numpy() * xt.double().cpu().numpy()[col]
+    sums = np.concatenate([[0.0], np.cumsum(prod.astype(np.longdouble))])
+    ref = (sums[row_ptr[1:]] - sums[row_ptr[:-1]]).astype(np.float64)
+    tol = 1e-5 if dtype == torch.float32 else 1e-12
+    # (the running long-double sum of 4M terms below 2.25 errs by under 2e-12)
+    assert np.all(np.abs(y - ref) <= tol * np.abs(ref) + 2e-12)
+    plan.close()
