@@ -164,14 +164,21 @@ void invalidate_graphs(merbit_plan* p) {
 // has no out-edge); built once per plan, shared by both PageRank drivers.
 int ensure_dmask(merbit_plan* p, hipStream_t st) {
   if (p->dmask) return MERBIT_OK;
+  // the plan gets the mask once it is built: a call that fails on the way
+  // leaves none behind
+  uint32_t* mask = nullptr;
   unsigned char* bytes = nullptr;
-  HIP_TRY(dev_alloc(&p->dmask, sizeof(uint32_t) * (size_t)((p->n_cols + 31) / 32 + 1)));
-  HIP_TRY(dev_alloc(&bytes, (size_t)(p->n_cols > 0 ? p->n_cols : 1)));
-  hipError_t e = launch_dangling_mask(p->col, p->nnz, p->n_cols, bytes, p->dmask, st);
-  hipError_t e2 = hipStreamSynchronize(st);
-  dev_free(bytes);
-  if (e != hipSuccess) return fail_hip("dangling mask", e);
-  if (e2 != hipSuccess) return fail_hip("dangling mask sync", e2);
+  hipError_t e = dev_alloc(&mask, sizeof(uint32_t) * (size_t)((p->n_cols + 31) / 32 + 1));
+  if (e == hipSuccess) e = dev_alloc(&bytes, (size_t)(p->n_cols > 0 ? p->n_cols : 1));
+  if (e == hipSuccess) e = launch_dangling_mask(p->col, p->nnz, p->n_cols, bytes, mask, st);
+  const hipError_t e2 = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = e2;
+  if (bytes) dev_free(bytes);
+  if (e != hipSuccess) {
+    if (mask) dev_free(mask);
+    return fail_hip("dangling mask", e);
+  }
+  p->dmask = mask;
   return MERBIT_OK;
 }
 

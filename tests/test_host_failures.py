@@ -1,0 +1,124 @@
+"""The library's host code under failures that a GPU run cannot bring about at
+will: a device allocation that fails in the middle of a call, and the calls
+after it.  The library's sources are compiled for the host only and linked with
+tests/host_runtime/fake_hip.hip, whose kernels are recorded and do nothing, so
+this runs without a GPU and checks no numbers."""
+import ctypes
+import os
+import re
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import numpy as np
+import pytest
+
+from conftest import ROOT
+from paper_2605_07391_amd import build as hipbuild
+from paper_2605_07391_amd import merbit as mb
+
+vp = ctypes.c_void_p
+N = 300
+
+
+@pytest.fixture(scope="session")
+def lib(tmp_path_factory):
+    """The library on the fake runtime."""
+    out = tmp_path_factory.mktemp("host_runtime")
+    flags = [f for f in hipbuild.FLAGS if f.startswith(("--offload-arch", "-std", "-fPIC", "-I"))]
+    sources = [os.path.join(hipbuild.CSRC, s) for s in hipbuild.SOURCES]
+    sources.append(os.path.join(ROOT, "tests", "host_runtime", "fake_hip.hip"))
+
+    def compile_(src):
+        obj = str(out / (os.path.basename(src) + ".o"))
+        subprocess.run([hipbuild.HIPCC, *flags, "-O0", "--offload-host-only", "-w",
+                        f"-I{hipbuild.CSRC}", "-c", src, "-o", obj], check=True)
+        return obj
+
+    with ThreadPoolExecutor(8) as pool:
+        objs = list(pool.map(compile_, sources))
+    # the device code that a host-only object refers to does not exist
+    names = subprocess.run(["nm", "-u", *objs], check=True, capture_output=True, text=True).stdout
+    stub = out / "fatbin.c"
+    stub.write_text("".join(f"char {n}[8];\n" for n in
+                            sorted(set(re.findall(r"\b__hip_fatbin_\w+", names)))))
+    so = str(out / "libmerbit_host.so")
+    wrap = ["_ZN6merbit15dev_alloc_bytesEPPvm", "_ZN6merbit8dev_freeEPv"]
+    subprocess.run(["g++", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-Wl,-z,defs",
+                    *[f"-Wl,--wrap={w}" for w in wrap], "-o", so, str(stub), *objs, "-lpthread"],
+                   check=True)
+    lib = ctypes.CDLL(so)
+    lib.fake_log.restype = ctypes.c_char_p
+    lib.fake_device_bytes.argtypes = [ctypes.c_size_t]
+    lib.fake_live_bytes.restype = ctypes.c_size_t
+    for f in ("fake_mallocs", "fake_frees", "fake_early_frees"):
+        getattr(lib, f).restype = ctypes.c_long
+    lib.fake_fail_new.argtypes = [ctypes.c_long]
+    lib.fake_capture.argtypes = [vp, ctypes.c_int]
+    lib.merbit_last_error.restype = ctypes.c_char_p
+    lib.merbit_plan_destroy.restype = None
+    return lib
+
+
+def _csr(n=N, per_row=3):
+    rp = (np.arange(n + 1) * per_row).astype(np.int32)
+    col = (np.arange(n * per_row) * 7 % n).astype(np.int32)
+    return rp, col, np.ones(len(col), np.float32)
+
+
+def _p(a):
+    return vp(a.ctypes.data)
+
+
+class HostPlan:
+    def __init__(self, lib, n=N, per_row=3, **kw):
+        self.lib, self.n = lib, n
+        self.keep = _csr(n, per_row)
+        rp, col, val = self.keep
+        o = mb.Opts()
+        lib.merbit_opts_init(ctypes.byref(o))
+        for k, v in {"hot_columns": 0, "validate": 0, "eager_loops": 1, **kw}.items():
+            setattr(o, k, v)
+        self.h = vp()
+        i64 = ctypes.c_int64
+        self.rc = lib.merbit_plan_create(i64(n), i64(n), i64(len(col)), _p(rp), _p(col), _p(val),
+                                         0, ctypes.byref(o), None, ctypes.byref(self.h))
+
+    def close(self):
+        self.lib.merbit_plan_destroy(self.h)
+        self.h = vp()
+
+
+def _launches(lib, call):
+    """(return code, [(kernel, what its line says of it)]) of one call."""
+    lib.fake_reset_log()
+    rc = call()
+    lines = lib.fake_log().decode().splitlines()
+    return rc, [tuple(x.split(" null:")) for x in lines]
+
+
+def _pagerank(lib, plan, x):
+    return lib.merbit_pagerank(plan.h, ctypes.c_double(0.85), ctypes.c_double(0.0), 3, 10, _p(x),
+                               None, None, None)
+
+
+# ------------------------------------------ calls after a failed one --
+
+@pytest.mark.parametrize("fault", ["first allocation", "second allocation", "synchronisation"])
+def test_dangling_mask_is_not_kept_unless_it_was_built(lib, fault):
+    """The mask of the dangling vertices is shared by all later calls: a call
+    that fails before its kernels have run must not leave it behind."""
+    plan = HostPlan(lib)
+    assert plan.rc == mb.OK
+    x = np.ones(N, np.float32)
+    if fault == "synchronisation":
+        lib.fake_fail_sync(1)
+    else:
+        lib.fake_fail_alloc(1 if fault == "first allocation" else 2)
+    rc, _ = _launches(lib, lambda: _pagerank(lib, plan, x))
+    assert rc == (mb.EHIP if fault == "synchronisation" else mb.ENOMEM)
+    rc, run = _launches(lib, lambda: _pagerank(lib, plan, x))
+    assert rc == mb.OK
+    assert "pack_dangling_kernel" in [k for k, _ in run], run
+    rc, run = _launches(lib, lambda: _pagerank(lib, plan, x))  # once built it is kept
+    assert rc == mb.OK and "pack_dangling_kernel" not in [k for k, _ in run]
+    plan.close()
