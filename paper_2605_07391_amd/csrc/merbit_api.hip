@@ -186,17 +186,16 @@ int ensure_pagerank_state(merbit_plan* p, hipStream_t st) {
   const size_t vb = vsize(p->dtype) * (size_t)p->n_rows;
   int rc = ensure_dmask(p, st);
   if (rc != MERBIT_OK) return rc;
-  if (!p->ybuf[0]) {
-    HIP_TRY(dev_alloc(&p->ybuf[0], vb));
-    HIP_TRY(dev_alloc(&p->ybuf[1], vb));
-    HIP_TRY(dev_alloc(&p->xwork, vb));
+  // (an earlier call may have run out of memory after some of them)
+  for (void*& y : p->ybuf) {
+    if (y) continue;
+    HIP_TRY(dev_alloc(&y, vb));
     p->zeroed_buf = -1;
   }
-  if (!p->partials[0]) {
-    p->reduce_grid = pr_reduce_grid(p->n_rows);
-    HIP_TRY(dev_alloc(&p->partials[0], 2 * sizeof(double) * (size_t)p->reduce_grid));
-    HIP_TRY(dev_alloc(&p->partials[1], 2 * sizeof(double) * (size_t)p->reduce_grid));
-  }
+  if (!p->xwork) HIP_TRY(dev_alloc(&p->xwork, vb));
+  p->reduce_grid = pr_reduce_grid(p->n_rows);
+  for (double*& v : p->partials)
+    if (!v) HIP_TRY(dev_alloc(&v, 2 * sizeof(double) * (size_t)p->reduce_grid));
   return MERBIT_OK;
 }
 

@@ -217,6 +217,7 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t q) {
   Lock l(mu());
+  if (!d || !s) return hipErrorInvalidValue;
   memcpy(d, s, n);
   st().pending.insert(q);
   return hipSuccess;

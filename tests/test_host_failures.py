@@ -122,3 +122,40 @@ def test_dangling_mask_is_not_kept_unless_it_was_built(lib, fault):
     rc, run = _launches(lib, lambda: _pagerank(lib, plan, x))  # once built it is kept
     assert rc == mb.OK and "pack_dangling_kernel" not in [k for k, _ in run]
     plan.close()
+
+
+def _check_calls_after_failures(lib, call, before=lambda plan: None):
+    """Fail each device allocation of `call` in turn on a new plan (used by
+    `before` first): the call reports it, and the next one succeeds and gives
+    every kernel the operands that it has on a plan which saw no failure."""
+    plan = HostPlan(lib)
+    before(plan)
+    rc, good = _launches(lib, lambda: call(plan))
+    plan.close()
+    assert rc == mb.OK
+    failures = 0
+    for nth in range(1, 40):
+        plan = HostPlan(lib)
+        before(plan)
+        lib.fake_fail_alloc(nth)
+        rc, _ = _launches(lib, lambda: call(plan))
+        lib.fake_fail_alloc(0)
+        if rc == mb.OK:  # fewer allocations than that
+            plan.close()
+            break
+        assert rc == mb.ENOMEM, lib.merbit_last_error()
+        failures += 1
+        # the same call, and one that uses what was there before
+        for again in (call, before):
+            rc, run = _launches(lib, lambda: again(plan))
+            assert rc in (mb.OK, None), lib.merbit_last_error()
+            if again is call:
+                assert set(run) <= set(good), (nth, set(run) - set(good))
+        plan.close()
+    return failures
+
+
+def test_pagerank_after_a_failed_allocation(lib):
+    x = np.ones(N, np.float32)
+    n = _check_calls_after_failures(lib, lambda plan: _pagerank(lib, plan, x))
+    assert n == 7  # the mask and its work space, three vectors, two pair arrays
