@@ -146,27 +146,31 @@ static int ensure_ppr_state(merbit_plan* p, int k, hipStream_t st) {
   if (p->ppr_k != k) {
     invalidate_graphs(p);
     HIP_TRY(hipDeviceSynchronize());  // earlier calls, on any stream
-    for (int b = 0; b < 3; ++b) {
-      if (p->pbuf[b]) dev_free(p->pbuf[b]);
-      p->pbuf[b] = nullptr;
+    // no width until all of its buffers are there: a call that runs out of
+    // memory on the way leaves none behind
+    p->ppr_k = 0;
+    p->ppr_zeroed = -1;
+    for (void*& v : p->pbuf) {
+      if (v) dev_free(v);
+      v = nullptr;
     }
     const size_t bytes = vsize(p->dtype) * (size_t)p->n_rows * (size_t)k;
     HIP_TRY(dev_alloc(&p->pbuf[0], bytes));
     if (k > kSlab) HIP_TRY(dev_alloc(&p->pbuf[1], bytes));
     HIP_TRY(dev_alloc(&p->pbuf[2], bytes));
     p->ppr_k = k;
-    p->ppr_zeroed = -1;
   }
+  // (an earlier call may have run out of memory after some of them)
+  p->ppr_grid_n = ppr_grid(p->n_rows);
   if (!p->ppart) {
-    p->ppr_grid_n = ppr_grid(p->n_rows);
     // the step's parts, then the first level of their sum
     const size_t rows = (size_t)spmm_blocks(p->tile_num) + (size_t)ppr_fixup_grid(p->tile_num) +
                         (size_t)p->ppr_grid_n + (size_t)ppr_sum_scratch_rows();
     HIP_TRY(dev_alloc(&p->ppart, sizeof(double) * 2 * 64 * rows));
-    HIP_TRY(dev_alloc(&p->psums[0], sizeof(double) * 2 * 64));
-    HIP_TRY(dev_alloc(&p->psums[1], sizeof(double) * 2 * 64));
-    HIP_TRY(dev_alloc(&p->psrc, sizeof(int32_t) * 64));
   }
+  for (double*& v : p->psums)
+    if (!v) HIP_TRY(dev_alloc(&v, sizeof(double) * 2 * 64));
+  if (!p->psrc) HIP_TRY(dev_alloc(&p->psrc, sizeof(int32_t) * 64));
   return MERBIT_OK;
 }
 

@@ -124,38 +124,60 @@ def test_dangling_mask_is_not_kept_unless_it_was_built(lib, fault):
     plan.close()
 
 
-def _check_calls_after_failures(lib, call, before=lambda plan: None):
-    """Fail each device allocation of `call` in turn on a new plan (used by
-    `before` first): the call reports it, and the next one succeeds and gives
-    every kernel the operands that it has on a plan which saw no failure."""
+def _check_calls_after_failures(lib, call, before=None):
+    """Fail each device allocation of `call` in turn on a new plan (which
+    `before` has used): the call reports it, and the calls after it, `call` or
+    `before` first, succeed and give every kernel the operands that it has on a
+    plan which saw no failure."""
+    good = {}
     plan = HostPlan(lib)
-    before(plan)
-    rc, good = _launches(lib, lambda: call(plan))
+    for c in [before, call] if before else [call]:
+        rc, run = _launches(lib, lambda: c(plan))
+        assert rc == mb.OK
+        good[c] = set(run)
     plan.close()
-    assert rc == mb.OK
     failures = 0
     for nth in range(1, 40):
-        plan = HostPlan(lib)
-        before(plan)
-        lib.fake_fail_alloc(nth)
-        rc, _ = _launches(lib, lambda: call(plan))
-        lib.fake_fail_alloc(0)
-        if rc == mb.OK:  # fewer allocations than that
+        for then in ([call, before], [before, call]) if before else ([call],):
+            plan = HostPlan(lib)
+            if before:
+                assert before(plan) == mb.OK
+            lib.fake_fail_alloc(nth)
+            rc = call(plan)
+            lib.fake_fail_alloc(0)
+            if rc == mb.OK:  # fewer allocations than that
+                plan.close()
+                return failures
+            assert rc == mb.ENOMEM, lib.merbit_last_error()
+            for c in then:
+                rc, run = _launches(lib, lambda: c(plan))
+                assert rc == mb.OK, lib.merbit_last_error()
+                assert set(run) <= good[c], (nth, set(run) - good[c])
             plan.close()
-            break
-        assert rc == mb.ENOMEM, lib.merbit_last_error()
         failures += 1
-        # the same call, and one that uses what was there before
-        for again in (call, before):
-            rc, run = _launches(lib, lambda: again(plan))
-            assert rc in (mb.OK, None), lib.merbit_last_error()
-            if again is call:
-                assert set(run) <= set(good), (nth, set(run) - set(good))
-        plan.close()
-    return failures
 
 
 def test_pagerank_after_a_failed_allocation(lib):
     x = np.ones(N, np.float32)
     n = _check_calls_after_failures(lib, lambda plan: _pagerank(lib, plan, x))
     assert n == 7  # the mask and its work space, three vectors, two pair arrays
+def _pagerank_personalized(lib, plan, x, k):
+    src = (np.arange(k) % plan.n).astype(np.int32)
+    return lib.merbit_pagerank_personalized(plan.h, ctypes.c_double(0.85), ctypes.c_double(0.0), 3,
+                                            10, _p(src), k, _p(x), None, None, None)
+
+
+@pytest.mark.parametrize("before_k", [0, 3, 40], ids=["new plan", "after k=3", "after k=40"])
+@pytest.mark.parametrize("k", [5, 64])
+def test_personalized_pagerank_after_a_failed_allocation(lib, k, before_k):
+    """Also with buffers of another width on the plan, and with a call of that
+    width after the failed one."""
+    x = np.ones((N, 64), np.float32)
+
+    def ppr(width):
+        return lambda plan: _pagerank_personalized(lib, plan, x, width)
+
+    n = _check_calls_after_failures(lib, ppr(k), ppr(before_k) if before_k else None)
+    # two or three vectors, and on a new plan the mask and its work space, the
+    # parts, two sums and the sources
+    assert n == (3 if k == 64 else 2) + (0 if before_k else 6)
