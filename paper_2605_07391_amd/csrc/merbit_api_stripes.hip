@@ -15,16 +15,19 @@ namespace {
 // front and handed out in 256-byte aligned parts; reset() hands the space out
 // again (the parts given before are dead: every user is on the build's one
 // stream, so later work is ordered after earlier reads), and a request
-// beyond the reserve gets an allocation of its own.  Everything is freed
-// when the build leaves (the build has waited for its stream by then).
+// beyond the reserve gets an allocation of its own.  Everything is freed when
+// the build leaves, by a return or an exception, once its stream's queued work
+// (which may use the space) is done.
 class Arena {
  public:
-  Arena() = default;
+  explicit Arena(hipStream_t st) : st_(st) {}
   Arena(const Arena&) = delete;
   Arena& operator=(const Arena&) = delete;
   ~Arena() {
+    (void)hipStreamSynchronize(st_);
     if (base_) dev_free(base_);
-    for (void* b : extra_) dev_free(b);
+    for (void* b : extra_)
+      if (b) dev_free(b);
   }
   hipError_t reserve(size_t bytes) {
     const hipError_t e = dev_alloc(&base_, bytes > 0 ? bytes : 1);
@@ -39,15 +42,16 @@ class Arena {
       used_ += b;
       return hipSuccess;
     }
-    void* q = nullptr;
+    extra_.push_back(nullptr);  // its place first: this may throw
+    void*& q = extra_.back();
     const hipError_t e = dev_alloc(&q, b > 0 ? b : 1);
-    if (e == hipSuccess) extra_.push_back(q);
     *out = static_cast<T*>(q);
     return e;
   }
   void reset() { used_ = 0; }
 
  private:
+  hipStream_t st_;
   unsigned char* base_ = nullptr;
   size_t cap_ = 0, used_ = 0;
   std::vector<void*> extra_;
@@ -326,7 +330,7 @@ static int build_range_hot(merbit_plan* p, int cap_req, hipStream_t st, Arena& t
 }
 
 int build_striped(merbit_plan* p, const int32_t* row_ptr, int hot_columns, hipStream_t st) {
-  Arena tmp;
+  Arena tmp(st);
   int rc = build_stripes(p, row_ptr, st, tmp);
   if (rc == MERBIT_OK) rc = build_range_hot(p, hot_columns, st, tmp);
   // the temporaries are freed on return: finish the work that reads them

@@ -40,6 +40,8 @@ struct State {
   std::map<void*, size_t> live;
   size_t live_bytes = 0, device_bytes = (size_t)1 << 40;
   long mallocs = 0, frees = 0, early_frees = 0;
+  long held = 0;     // library blocks allocated and not yet given up
+  int32_t fill = 0;  // what new device memory holds
   std::set<hipStream_t> pending;
   hipStream_t capturing = nullptr;
   bool any_capture = false;
@@ -123,6 +125,8 @@ size_t fake_live_bytes() { return st().live_bytes; }
 long fake_mallocs() { return st().mallocs; }
 long fake_frees() { return st().frees; }
 long fake_early_frees() { return st().early_frees; }
+long fake_held() { return st().held; }
+void fake_fill(int v) { st().fill = v; }
 void fake_capture(void* stream, int on) {
   st().any_capture = on != 0;
   st().capturing = static_cast<hipStream_t>(stream);
@@ -192,7 +196,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   ++st().mallocs;
   if (st().live_bytes + n > st().device_bytes) return hipErrorOutOfMemory;
   *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
-  memset(*p, 0, n);
+  for (size_t i = 0; i < n / 4; ++i) static_cast<int32_t*>(*p)[i] = st().fill;
   st().live[*p] = n;
   st().live_bytes += n;
   return hipSuccess;
@@ -337,12 +341,16 @@ hipError_t __wrap__ZN6merbit15dev_alloc_bytesEPPvm(void** out, size_t bytes) {
       return hipErrorOutOfMemory;
     }
   }
-  return __real__ZN6merbit15dev_alloc_bytesEPPvm(out, bytes);
+  const hipError_t e = __real__ZN6merbit15dev_alloc_bytesEPPvm(out, bytes);
+  Lock l(mu());
+  if (e == hipSuccess) ++st().held;
+  return e;
 }
 void __real__ZN6merbit8dev_freeEPv(void* p) noexcept;
 void __wrap__ZN6merbit8dev_freeEPv(void* p) noexcept {
   {
     Lock l(mu());
+    if (p) --st().held;
     if (p && !st().pending.empty()) ++st().early_frees;
   }
   __real__ZN6merbit8dev_freeEPv(p);

@@ -50,7 +50,7 @@ def lib(tmp_path_factory):
     lib.fake_log.restype = ctypes.c_char_p
     lib.fake_device_bytes.argtypes = [ctypes.c_size_t]
     lib.fake_live_bytes.restype = ctypes.c_size_t
-    for f in ("fake_mallocs", "fake_frees", "fake_early_frees"):
+    for f in ("fake_mallocs", "fake_frees", "fake_early_frees", "fake_held"):
         getattr(lib, f).restype = ctypes.c_long
     lib.fake_fail_new.argtypes = [ctypes.c_long]
     lib.fake_capture.argtypes = [vp, ctypes.c_int]
@@ -181,3 +181,25 @@ def test_personalized_pagerank_after_a_failed_allocation(lib, k, before_k):
     # two or three vectors, and on a new plan the mask and its work space, the
     # parts, two sums and the sources
     assert n == (3 if k == 64 else 2) + (0 if before_k else 6)
+
+
+# ------------------------------------------------- memory and pending work --
+
+def test_host_memory_runs_out_during_a_striped_build(lib):
+    """The build's temporaries go back while an exception unwinds it: only
+    after its queued work, and all of them."""
+    lib.fake_fill(1)  # one (stripe, row) pair and one more: a plan of two rows
+    failures = 0
+    for nth in range(1, 400):
+        held, early = lib.fake_held(), lib.fake_early_frees()
+        lib.fake_fail_new(nth)
+        plan = HostPlan(lib, stripes=8, hot_columns=-1)
+        lib.fake_fail_new(0)
+        if lib.merbit_last_error() != b"host memory exhausted":
+            break
+        failures += 1
+        assert plan.rc == mb.ENOMEM and not plan.h.value
+        assert lib.fake_early_frees() == early, nth
+        assert lib.fake_held() == held, nth
+    lib.fake_fill(0)
+    assert failures >= 20
