@@ -141,9 +141,9 @@ inline size_t vsize(int dtype) { return dtype == MERBIT_F64 ? sizeof(double) : s
 // Device memory of plans and temporaries (merbit_mem.hip): freed blocks are
 // kept for reuse, within a bound.  Free a block only when no work that uses it
 // is pending on any stream.
-hipError_t dev_alloc_bytes(void** out, size_t bytes);
+hipError_t dev_alloc_bytes(void** out, size_t bytes) noexcept;
 template <typename T>
-hipError_t dev_alloc(T** out, size_t bytes) {
+hipError_t dev_alloc(T** out, size_t bytes) noexcept {
   void* q = nullptr;
   const hipError_t e = dev_alloc_bytes(&q, bytes);
   *out = static_cast<T*>(q);

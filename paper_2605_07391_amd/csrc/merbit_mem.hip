@@ -63,7 +63,7 @@ size_t rounded(size_t bytes) {
 
 }  // namespace
 
-hipError_t dev_alloc_bytes(void** out, size_t bytes) {
+hipError_t dev_alloc_bytes(void** out, size_t bytes) noexcept try {
   *out = nullptr;
   int device = 0;
   hipError_t e = hipGetDevice(&device);
@@ -104,6 +104,10 @@ hipError_t dev_alloc_bytes(void** out, size_t bytes) {
   }
   *out = b.ptr;
   return hipSuccess;
+} catch (...) {
+  // the records of the blocks are host memory: to the callers, which hold other
+  // blocks to give up, its end is one more failed allocation
+  return hipErrorOutOfMemory;
 }
 
 void dev_free(void* ptr) noexcept {

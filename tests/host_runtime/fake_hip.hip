@@ -119,7 +119,12 @@ void fake_reset_log() {
 const char* fake_log() { return st().log.c_str(); }
 void fake_fail_alloc(int n) { st().fail_alloc = n; }
 void fake_fail_sync(int n) { st().fail_sync = n; }
-void fake_fail_new(long n) { g_fail_new = n; }
+// returns what was left of the count before: > 0 if the failure did not come
+long fake_fail_new(long n) {
+  const long left = g_fail_new;
+  g_fail_new = n;
+  return left;
+}
 void fake_device_bytes(size_t n) { st().device_bytes = n; }
 size_t fake_live_bytes() { return st().live_bytes; }
 long fake_mallocs() { return st().mallocs; }
