@@ -10,6 +10,7 @@
 //     have not reused goes back as well;
 //   - given back: when an allocation fails, everything kept is returned to the
 //     device and the allocation tried again;
+//   - not under capture: where hipMalloc is refused, so is a kept block;
 //   - no work pending: a caller frees a block only after it has waited for the
 //     work that uses it (the streams of the call, or the device), so a block
 //     can be handed to any stream; dev_free itself does not wait;
@@ -68,6 +69,12 @@ hipError_t dev_alloc_bytes(void** out, size_t bytes) noexcept try {
   int device = 0;
   hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return e;
+  // a kept block is handed out only where hipMalloc would be allowed: it is
+  // refused while a stream is captured (by this thread, or by any in global
+  // mode), and a call that went on would have its kernels recorded with memory
+  // that it gives up when it returns.  Size 0 allocates nothing (0.3 us).
+  void* none = nullptr;
+  if ((e = hipMalloc(&none, 0)) != hipSuccess) return e;
   const size_t want = rounded(bytes > 0 ? bytes : 1);
   Pool& p = pool();
   std::lock_guard<std::mutex> lock(p.mu);

@@ -198,6 +198,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   Lock l(mu());
   *p = nullptr;
   if (st().any_capture) return hipErrorStreamCaptureUnsupported;
+  if (n == 0) return hipSuccess;
   ++st().mallocs;
   if (st().live_bytes + n > st().device_bytes) return hipErrorOutOfMemory;
   *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);

@@ -228,3 +228,31 @@ def test_host_memory_runs_out_during_a_striped_build(lib):
         assert lib.fake_held() == held, nth
     lib.fake_fill(0)
     assert failures >= 20
+
+
+@pytest.mark.parametrize("call", ["plan_create", "transpose"])
+def test_calls_that_allocate_are_refused_under_capture(lib, call):
+    """While a stream is captured hipMalloc is refused, and with it every call
+    that needs memory -- also where a kept block would do: its kernels would
+    only be recorded, and the recording would outlive the block."""
+    rp_t, col_t, perm = np.zeros(N + 1, np.int32), np.zeros(3 * N, np.int32), np.zeros(3 * N, np.int32)
+
+    def transpose(plan):
+        return lib.merbit_transpose(plan.h, _p(rp_t), _p(col_t), _p(perm), None)
+
+    plan = HostPlan(lib)
+    assert transpose(plan) == mb.OK
+    HostPlan(lib).close()  # blocks of every size are kept now
+    held = lib.fake_held()
+    lib.fake_capture(None, 1)
+    if call == "plan_create":
+        again = HostPlan(lib)
+        rc, launched = again.rc, bool(again.h)
+    else:
+        rc, run = _launches(lib, lambda: transpose(plan))
+        launched = bool(run)
+    lib.fake_capture(None, 0)
+    assert rc == mb.EHIP and not launched
+    assert lib.fake_held() == held
+    assert transpose(plan) == mb.OK
+    plan.close()
