@@ -51,8 +51,8 @@ void plan_free_all(merbit_plan* p) {
   // the plan's blocks may go to any stream next: wait for its device
   int dev = 0;
   const bool other = hipGetDevice(&dev) == hipSuccess && dev != p->device;
-  if (other) (void)hipSetDevice(p->device);
-  (void)hipDeviceSynchronize();
+  hipError_t waited = other ? hipSetDevice(p->device) : hipSuccess;
+  if (waited == hipSuccess) waited = hipDeviceSynchronize();
   if (other) (void)hipSetDevice(dev);
   drop_graphs(p);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
@@ -66,7 +66,7 @@ void plan_free_all(merbit_plan* p) {
                   p->bpart[4], p->bpart[5], p->bpart[6], p->sperm, p->scol, p->svals, p->swords,
                   p->yv[0], p->yv[1], p->range_tile, p->hot_off};
   for (void* b : bufs)
-    if (b) dev_free(b);
+    if (b) dev_free_after(waited, b);
   for (auto& ev : p->events) {
     (void)hipEventDestroy(ev.first);
     (void)hipEventDestroy(ev.second);
@@ -173,9 +173,9 @@ int ensure_dmask(merbit_plan* p, hipStream_t st) {
   if (e == hipSuccess) e = launch_dangling_mask(p->col, p->nnz, p->n_cols, bytes, mask, st);
   const hipError_t e2 = hipStreamSynchronize(st);
   if (e == hipSuccess) e = e2;
-  if (bytes) dev_free(bytes);
+  if (bytes) dev_free_after(e2, bytes);
   if (e != hipSuccess) {
-    if (mask) dev_free(mask);
+    if (mask) dev_free_after(e2, mask);
     return fail_hip("dangling mask", e);
   }
   p->dmask = mask;
@@ -347,8 +347,8 @@ static int build_hot_cache(merbit_plan* p, int cap_req, hipStream_t st) {
     const size_t wb = (hot_select_layout(&seg, 1) + 255) & ~(size_t)255;
     unsigned char* tmp = nullptr;
     auto release = [&]() {
-      (void)hipStreamSynchronize(st);
-      if (tmp) dev_free(tmp);
+      const hipError_t waited = hipStreamSynchronize(st);
+      if (tmp) dev_free_after(waited, tmp);
     };
     hipError_t e = dev_alloc(&tmp, wb + sizeof(HotSel));
     HotSel* sel_dev = reinterpret_cast<HotSel*>(tmp + wb);
@@ -374,8 +374,7 @@ static int build_hot_cache(merbit_plan* p, int cap_req, hipStream_t st) {
       if (e == hipSuccess) e = dev_alloc(&p->x_hot, vs * (size_t)taken);
       if (e == hipSuccess) p->hot_n = (int32_t)taken;
     } else {
-      (void)hipStreamSynchronize(st);
-      dev_free(p->hot_cols);
+      dev_free_after(hipStreamSynchronize(st), p->hot_cols);
       p->hot_cols = nullptr;
     }
     release();

@@ -45,8 +45,8 @@ int merbit_transpose(merbit_plan* p, int32_t* rowT_ptr, int32_t* colT, int32_t* 
   }
   if (e == hipSuccess)
     e = launch_transpose(p->col, m, p->n_cols, end_bit, tmp, rowT_ptr, colT, perm, st);
-  (void)hipStreamSynchronize(st);
-  if (tmp) dev_free(tmp);
+  const hipError_t waited = hipStreamSynchronize(st);
+  if (tmp) dev_free_after(waited, tmp);
   if (e != hipSuccess) return fail_hip("transpose", e);
   p->last_stream = st;
   return MERBIT_OK;

@@ -24,10 +24,10 @@ class Arena {
   Arena(const Arena&) = delete;
   Arena& operator=(const Arena&) = delete;
   ~Arena() {
-    (void)hipStreamSynchronize(st_);
-    if (base_) dev_free(base_);
+    const hipError_t waited = hipStreamSynchronize(st_);
+    if (base_) dev_free_after(waited, base_);
     for (void* b : extra_)
-      if (b) dev_free(b);
+      if (b) dev_free_after(waited, b);
   }
   hipError_t reserve(size_t bytes) {
     const hipError_t e = dev_alloc(&base_, bytes > 0 ? bytes : 1);

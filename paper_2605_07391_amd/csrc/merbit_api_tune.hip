@@ -38,10 +38,10 @@ int merbit_tune(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t* row_
   void *x = nullptr, *y0 = nullptr, *y1 = nullptr;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   auto cleanup = [&]() {
-    (void)hipStreamSynchronize(st);  // x's fill, the last candidate's launches
-    if (x) dev_free(x);
-    if (y0) dev_free(y0);
-    if (y1) dev_free(y1);
+    // x's fill, the last candidate's launches
+    const hipError_t waited = hipStreamSynchronize(st);
+    for (void* b : {x, y0, y1})
+      if (b) dev_free_after(waited, b);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
   };

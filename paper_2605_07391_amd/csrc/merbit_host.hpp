@@ -150,6 +150,10 @@ hipError_t dev_alloc(T** out, size_t bytes) noexcept {
   return e;
 }
 void dev_free(void* ptr) noexcept;
+// Give up a block after waiting for the work that uses it, `waited` being what
+// the wait returned: if it failed, work may still be pending, and the block
+// goes back to the device (whose hipFree waits) instead of to the next caller.
+void dev_free_after(hipError_t waited, void* ptr) noexcept;
 
 void plan_free_all(merbit_plan* p);
 // The fused SpMV y = A x (z: the other dual buffer, cleared at boundary rows,

@@ -142,4 +142,15 @@ void dev_free(void* ptr) noexcept {
     p.give_back(0);
 }
 
+void dev_free_after(hipError_t waited, void* ptr) noexcept {
+  if (waited == hipSuccess) return dev_free(ptr);
+  if (!ptr) return;
+  {
+    Pool& p = pool();
+    std::lock_guard<std::mutex> lock(p.mu);
+    if (p.live.erase(ptr) == 0) return;  // not ours
+  }
+  (void)hipFree(ptr);
+}
+
 }  // namespace merbit

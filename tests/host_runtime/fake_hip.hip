@@ -361,6 +361,15 @@ void __wrap__ZN6merbit8dev_freeEPv(void* p) noexcept {
   }
   __real__ZN6merbit8dev_freeEPv(p);
 }
+void __real__ZN6merbit14dev_free_afterE10hipError_tPv(hipError_t waited, void* p) noexcept;
+void __wrap__ZN6merbit14dev_free_afterE10hipError_tPv(hipError_t waited, void* p) noexcept {
+  {
+    Lock l(mu());
+    if (p) --st().held;
+    if (p && waited == hipSuccess && !st().pending.empty()) ++st().early_frees;
+  }
+  __real__ZN6merbit14dev_free_afterE10hipError_tPv(waited, p);
+}
 
 }  // extern "C"
 

@@ -42,7 +42,8 @@ def lib(tmp_path_factory):
     stub.write_text("".join(f"char {n}[8];\n" for n in
                             sorted(set(re.findall(r"\b__hip_fatbin_\w+", names)))))
     so = str(out / "libmerbit_host.so")
-    wrap = ["_ZN6merbit15dev_alloc_bytesEPPvm", "_ZN6merbit8dev_freeEPv"]
+    wrap = ["_ZN6merbit15dev_alloc_bytesEPPvm", "_ZN6merbit8dev_freeEPv",
+            "_ZN6merbit14dev_free_afterE10hipError_tPv"]
     subprocess.run(["g++", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-Wl,-z,defs",
                     *[f"-Wl,--wrap={w}" for w in wrap], "-o", so, str(stub), *objs, "-lpthread"],
                    check=True)
@@ -255,4 +256,31 @@ def test_calls_that_allocate_are_refused_under_capture(lib, call):
     assert rc == mb.EHIP and not launched
     assert lib.fake_held() == held
     assert transpose(plan) == mb.OK
+    plan.close()
+
+
+@pytest.mark.parametrize("call", ["plan_destroy", "transpose", "dangling mask", "tune"])
+def test_blocks_whose_work_was_not_waited_for_are_not_reused(lib, call):
+    """A wait that fails (or is refused, under capture) leaves work pending:
+    the blocks it uses go back to the device and not to the next caller."""
+    x = np.ones(N, np.float32)
+    rp_t, col_t, perm = np.zeros(N + 1, np.int32), np.zeros(3 * N, np.int32), np.zeros(3 * N, np.int32)
+    plan = HostPlan(lib)
+    early, frees = lib.fake_early_frees(), lib.fake_frees()
+    if call == "plan_destroy":
+        assert lib.merbit_spmv(plan.h, _p(x), _p(np.ones(N, np.float32)), None) == mb.OK
+        lib.fake_fail_sync(1)
+        plan.close()
+    elif call == "transpose":
+        lib.fake_fail_sync(1)
+        lib.merbit_transpose(plan.h, _p(rp_t), _p(col_t), _p(perm), None)
+    elif call == "dangling mask":
+        lib.fake_fail_sync(1)
+        assert _pagerank(lib, plan, x) == mb.EHIP
+    else:
+        lib.fake_fail_sync(1)
+        _tune(lib)
+    assert lib.fake_early_frees() == early
+    assert lib.fake_frees() > frees
+    lib.fake_fail_sync(0)
     plan.close()
