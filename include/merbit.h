@@ -436,10 +436,19 @@ int merbit_profile_enable(merbit_plan* plan, int enable);
 int merbit_profile_read(merbit_plan* plan, int64_t* launches, double* total_ms);
 
 /* Release the plan and everything it owns (waits for its pending work).  The
- * library keeps up to 512 MiB of freed device memory for the plans and
- * temporaries of later calls; it returns all of it to the device when an
- * allocation fails, and blocks that go unused for long or exceed the bound. */
+ * library keeps up to 512 MiB of freed device memory, over all devices, for the
+ * plans and temporaries of later calls.  It returns the blocks that exceed the
+ * bound or that 512 of its own later allocations and frees have not reused, and
+ * all of them when one of its allocations fails or merbit_release_memory is
+ * called.  A kept block serves requests down to three quarters of its size. */
 void merbit_plan_destroy(merbit_plan* plan);
+
+/* Return the freed device memory that the library keeps (see
+ * merbit_plan_destroy) to the devices, for instance when no more plans are
+ * built or when another allocator of the process needs it; the memory of
+ * existing plans is not touched.  Returns the number of bytes.  May be called
+ * from any thread; waits for the devices, as hipFree does. */
+int64_t merbit_release_memory(void);
 
 /* Message of the last failed call on this thread ("" if none). */
 const char* merbit_last_error(void);

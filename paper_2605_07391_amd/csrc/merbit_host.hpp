@@ -154,6 +154,8 @@ void dev_free(void* ptr) noexcept;
 // the wait returned: if it failed, work may still be pending, and the block
 // goes back to the device (whose hipFree waits) instead of to the next caller.
 void dev_free_after(hipError_t waited, void* ptr) noexcept;
+// Return the kept blocks to the device; the bytes returned.
+size_t dev_release() noexcept;
 
 void plan_free_all(merbit_plan* p);
 // The fused SpMV y = A x (z: the other dual buffer, cleared at boundary rows,

@@ -25,7 +25,8 @@ EXPORTED = ("merbit_opts_init", "merbit_plan_create", "merbit_plan_set_values", 
             "merbit_sddmm", "merbit_gather_values", "merbit_column_scale",
             "merbit_pagerank_adjoint", "merbit_bicgstab", "merbit_tune",
             "merbit_profile_enable", "merbit_profile_read",
-            "merbit_plan_destroy", "merbit_last_error", "merbit_version")
+            "merbit_plan_destroy", "merbit_release_memory", "merbit_last_error",
+            "merbit_version")
 
 
 class MerbitError(RuntimeError):
@@ -109,6 +110,8 @@ def load():
     lib.merbit_profile_read.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(dbl)]
     lib.merbit_plan_destroy.argtypes = [vp]
     lib.merbit_plan_destroy.restype = None
+    lib.merbit_release_memory.argtypes = []
+    lib.merbit_release_memory.restype = i64
     lib.merbit_last_error.restype = ctypes.c_char_p
     lib.merbit_version.restype = ctypes.c_char_p
     for name in ("merbit_plan_create", "merbit_plan_set_values", "merbit_plan_info",
@@ -533,6 +536,12 @@ def tune(row_ptr: torch.Tensor, col_ind: torch.Tensor, values: torch.Tensor, n_c
     table = {(int(s), int(b)): float(us[i * bl.size + j])
              for i, s in enumerate(sg) for j, b in enumerate(bl)}
     return {"sigma": opts.sigma, "block_lanes": opts.block_lanes}, table
+
+
+def release_memory() -> int:
+    """Return the freed device memory that the library keeps for later plans
+    and temporaries (at most 512 MiB) to the devices; the bytes returned."""
+    return load().merbit_release_memory()
 
 
 def version() -> str:

@@ -16,6 +16,10 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <sys/mman.h>
+
+#include <chrono>
+#include <condition_variable>
 #include <map>
 #include <mutex>
 #include <new>
@@ -61,6 +65,16 @@ std::recursive_mutex& mu() {
   return *m;
 }
 typedef std::lock_guard<std::recursive_mutex> Lock;
+std::mutex& gate_mu() {
+  static std::mutex* m = new std::mutex();
+  return *m;
+}
+std::condition_variable& gate_cv() {
+  static std::condition_variable* c = new std::condition_variable();
+  return *c;
+}
+bool g_gate = false;
+long g_gate_timeouts = 0, g_gate_waiting = 0;
 thread_local long g_fail_new = 0;
 
 bool countdown(int& n) {
@@ -130,6 +144,13 @@ size_t fake_live_bytes() { return st().live_bytes; }
 long fake_mallocs() { return st().mallocs; }
 long fake_frees() { return st().frees; }
 long fake_early_frees() { return st().early_frees; }
+void fake_gate(int on) {
+  std::lock_guard<std::mutex> g(gate_mu());
+  g_gate = on != 0;
+  gate_cv().notify_all();
+}
+long fake_gate_waiting() { return g_gate_waiting; }
+long fake_gate_timeouts() { return g_gate_timeouts; }
 long fake_held() { return st().held; }
 void fake_fill(int v) { st().fill = v; }
 void fake_capture(void* stream, int on) {
@@ -201,13 +222,21 @@ hipError_t hipMalloc(void** p, size_t n) {
   if (n == 0) return hipSuccess;
   ++st().mallocs;
   if (st().live_bytes + n > st().device_bytes) return hipErrorOutOfMemory;
-  *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
-  for (size_t i = 0; i < n / 4; ++i) static_cast<int32_t*>(*p)[i] = st().fill;
+  *p = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  if (*p == MAP_FAILED) abort();
+  for (size_t i = 0; st().fill != 0 && i < n / 4; ++i) static_cast<int32_t*>(*p)[i] = st().fill;
   st().live[*p] = n;
   st().live_bytes += n;
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
+  {
+    // a device that is busy until fake_gate(0) (or for five seconds)
+    std::unique_lock<std::mutex> g(gate_mu());
+    if (g_gate) ++g_gate_waiting;
+    if (g_gate && !gate_cv().wait_for(g, std::chrono::seconds(5), [] { return !g_gate; }))
+      ++g_gate_timeouts;
+  }
   Lock l(mu());
   if (st().any_capture) return hipErrorStreamCaptureUnsupported;
   auto it = st().live.find(p);
@@ -215,8 +244,8 @@ hipError_t hipFree(void* p) {
   st().pending.clear();  // waits for the device
   st().live_bytes -= it->second;
   ++st().frees;
+  munmap(p, it->second);
   st().live.erase(it);
-  free(p);
   return hipSuccess;
 }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
