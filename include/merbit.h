@@ -66,8 +66,9 @@ typedef struct {
     int32_t block_lanes;   /* threads per block; 0 = WAVE: 1024 (FP32, 32-bit
                               descriptors) or 512, BLOCK: 256 (a WAVE plan of the default
                               size without stripes that ends up without a hot cache is
-                              launched in blocks of 256).  Built: BLOCK 128, 256, 512,
-                              1024; WAVE 256, 512, 1024 (64-bit: 256, 512)             */
+                              launched in blocks of 256, unless blocks_per_cu is given).
+                              Built: BLOCK 128, 256, 512, 1024; WAVE 256, 512, 1024
+                              (64-bit: 256, 512)                                       */
     int32_t commit;        /* merbit_commit                                            */
     int32_t hot_columns;   /* LDS x cache for the most frequent columns -- an addition
                               to the paper's method: on gfx950 scattered x gathers are
@@ -85,8 +86,9 @@ typedef struct {
                               their order are unchanged.                                */
     int32_t validate;      /* nonzero: check the CSR on the device first (one host
                               synchronisation); MERBIT_EINVAL if it is malformed        */
-    int32_t blocks_per_cu; /* resident blocks per CU for the persistent launches;
-                              0 = as many as LDS and wavefront slots allow              */
+    int32_t blocks_per_cu; /* resident blocks (of block_lanes threads) per CU for the
+                              persistent launches; 0 = as many as LDS, registers and
+                              wavefront slots allow                                     */
     int32_t eager_loops;   /* 0: the PageRank drivers record each chunk of iterations
                               between two convergence checks into a HIP graph on first
                               use and replay it; nonzero: launch every kernel directly  */

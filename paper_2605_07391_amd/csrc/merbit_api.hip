@@ -226,7 +226,8 @@ constexpr int kPlainWaves = 4;
 // blocks (block b runs on XCD b mod 8) one contiguous range of tiles.
 //
 // A wave plan of the default block size that has no hot cache is launched in
-// blocks of 4 wavefronts: larger blocks only serve to share the cache.  A
+// blocks of 4 wavefronts: larger blocks only serve to share the cache (with a
+// limit of blocks per CU, which counts blocks of the plan's size, it is not).  A
 // small plan then spreads over the chip (124 tiles as 31 blocks instead of 8
 // blocks of 16 wavefronts, 4 on each SIMD) and a middle-sized one fills it
 // (R-MAT 18: with 1,024 lanes one block fits per CU, and the last of 342
@@ -236,7 +237,7 @@ constexpr int kPlainWaves = 4;
 int size_grid(merbit_plan* p) {
   p->launch_waves = p->waves;
   if (p->commit == MERBIT_COMMIT_WAVE && p->stripes <= 1 && p->hot_n == 0 && !p->lanes_given &&
-      p->waves > kPlainWaves)
+      p->blocks_per_cu_req == 0 && p->waves > kPlainWaves)
     p->launch_waves = kPlainWaves;
   const int waves = p->launch_waves;
   p->unit_tiles = p->commit == MERBIT_COMMIT_WAVE ? 1 : p->waves;

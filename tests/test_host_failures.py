@@ -346,3 +346,28 @@ def test_other_threads_go_on_while_memory_goes_back(lib):
     releasing.join()
     assert plan.rc == mb.OK and lib.fake_gate_timeouts() == timeouts
     plan.close()
+
+
+# ------------------------------------------------------------ launch shape --
+
+def _launch_shape(lib, plan):
+    x, y = np.ones(plan.n, np.float32), np.ones(plan.n, np.float32)
+    rc, run = _launches(lib, lambda: lib.merbit_spmv(plan.h, _p(x), _p(y), None))
+    assert rc == mb.OK
+    last = [what for k, what in run if k.startswith("spmv")][-1]
+    return tuple(int(v) for v in re.search(r"block: (\d+) grid: (\d+)", last).groups())
+
+
+@pytest.mark.parametrize("options,shape", [
+    (dict(blocks_per_cu=1), (1024, 256)),
+    (dict(blocks_per_cu=1, desc_bits=64, sigma=16), (512, 256)),
+    (dict(blocks_per_cu=1, block_lanes=256), (256, 256)),
+    (dict(), (256, 4 * 256)),
+], ids=["default lanes", "default lanes, 64 bits", "256 lanes", "no limit"])
+def test_blocks_per_cu_counts_blocks_of_the_plans_size(lib, options, shape):
+    """One resident block per CU is one of block_lanes (of its default when not
+    given), on a plan with more tiles than the 256 CUs can hold."""
+    plan = HostPlan(lib, n=3_000_000, per_row=1, **options)
+    assert plan.rc == mb.OK
+    assert _launch_shape(lib, plan) == shape
+    plan.close()
