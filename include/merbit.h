@@ -135,7 +135,8 @@ typedef struct {
     int32_t hot_columns;   /* columns whose x values are served from LDS (0 = none)     */
     int32_t omega;         /* lanes per tile = wavefront size = 64                      */
     int32_t sigma;         /* merge-path steps per lane                     Sec. 4.3    */
-    int32_t block_lanes;   /* lanes (threads) per block, b of Sec. 4.3                  */
+    int32_t block_lanes;   /* lanes (threads) per block of the fused launch, b of Sec.
+                              4.3: the plan option, or what became of its default      */
     int32_t offset_bits;   /* ceil(log2(omega sigma)), width of x_offset / y_offset     */
     int32_t dtype;         /* merbit_dtype                                              */
     int32_t lds_bytes;     /* LDS per block: (b sigma + 1) values for products and row

@@ -618,7 +618,7 @@ int merbit_plan_info(merbit_plan* p, merbit_plan_info_t* info) try {
   info->hot_coverage = p->hot_coverage;
   info->omega = kOmega;
   info->sigma = p->sigma;
-  info->block_lanes = p->block_lanes;
+  info->block_lanes = p->launch_waves * kOmega;
   info->offset_bits = p->bits;
   info->dtype = p->dtype;
   info->lds_bytes = (int32_t)(static_lds_bytes(p) + p->hot_lds_bytes);

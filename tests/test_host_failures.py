@@ -371,3 +371,16 @@ def test_blocks_per_cu_counts_blocks_of_the_plans_size(lib, options, shape):
     assert plan.rc == mb.OK
     assert _launch_shape(lib, plan) == shape
     plan.close()
+
+
+@pytest.mark.parametrize("options", [dict(), dict(blocks_per_cu=1), dict(block_lanes=512),
+                                     dict(desc_bits=64, sigma=16), dict(commit=1)],
+                         ids=["default", "limit", "512 lanes", "64 bits", "block commit"])
+def test_plan_info_describes_the_launch(lib, options):
+    plan = HostPlan(lib, n=100_000, **options)
+    info = mb.PlanInfo()
+    assert lib.merbit_plan_info(plan.h, ctypes.byref(info)) == mb.OK
+    assert (info.block_lanes, info.grid) == _launch_shape(lib, plan)
+    # one FP32 value per merge-path step of the block, and the kernel's few words
+    assert 0 <= info.lds_bytes - 4 * info.block_lanes * info.sigma <= 64 + 4 * 33
+    plan.close()
