@@ -561,3 +561,50 @@ def test_pagerank_multi_chunk_sums(rows, dtype):
         rel = np.abs(x.double().cpu().numpy() - ref[iters]) / ref[iters]
         assert rel.max() <= PR_TOL[dtype], rel.max()
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+@pytest.mark.parametrize("which", ["X", "Y", "Z", "all"])
+@pytest.mark.parametrize("k", [4, 8, 32, 36])
+def test_spmm_operand_base_not_16_byte_aligned(k, which, dtype):
+    """Columns 1 .. k of arrays whose row pitch allows wide accesses: the base
+    of one operand does not, and the columns beside them stay as they are."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    rng = np.random.default_rng(k)
+    lens = np.concatenate([[900], rng.integers(0, 6, 400), np.zeros(60, int), [200, 1]])
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n, nc = len(rp) - 1, 333
+    col = rng.integers(0, nc, rp[-1]).astype(np.int32)
+    vals = rng.uniform(-1, 1, rp[-1])
+    r, c, v = to_device(rp, col, vals, dtype, dev)
+    plan = pkg.Plan(r, c, v, nc, sigma=5)
+
+    def operand(name, rows):
+        off = 1 if which in (name, "all") else 0
+        wide = torch.full((rows, k + 4), float("nan"), dtype=dtype, device=dev)
+        part = wide[:, off:off + k]
+        assert part.data_ptr() % 16 == (off * wide.element_size()) % 16
+        return wide, part, off
+
+    Xw, X, _ = operand("X", nc)
+    Yw, Y, y0 = operand("Y", n)
+    Zw, Z, z0 = operand("Z", n)
+    for it in range(3):
+        X64 = seeded_X(nc, k, 40 + it, dtype)
+        X.copy_(torch.from_numpy(X64).to(dtype))
+        if it == 0:
+            plan.spmm(X, out=Y)
+            got, wide, off = Y, Yw, y0
+            plan.spmm_zero_boundary(Z)
+        elif it == 1:
+            plan.spmm_dual(X, Z, Y)
+            got, wide, off = Z, Zw, z0
+        else:
+            plan.spmm_dual(X, Y, Z)
+            got, wide, off = Y, Yw, y0
+        torch.cuda.synchronize()
+        check_spmm(got, rp, col, host_values(vals, dtype), X64, dtype, f"step {it}")
+        beside = torch.cat([wide[:, :off], wide[:, off + k:]], 1)
+        assert torch.isnan(beside).all()
+    plan.close()
