@@ -544,3 +544,65 @@ def test_rows_finished_by_the_tile_they_end_in(longest, stripes, hot, sigma, des
             torch.cuda.synchronize()
             check_spmv(z, rp, col, host_values(vals, dtype), x64, dtype, "dual 1")
         plan.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+@pytest.mark.parametrize("sigma,desc_bits", [(1, 32), (7, 32), (12, 32), (16, 64)])
+@pytest.mark.parametrize("hot", [0, 40])
+@pytest.mark.parametrize("longest", [129, 3000])
+def test_dual_launch_clears_the_rows_it_is_added_to(longest, hot, sigma, desc_bits, dtype):
+    """The second of two dual-buffer launches adds its long rows onto what the
+    first left in z, which was NaN throughout: every first row of a tile must
+    have been cleared, and every other row is stored whole."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    rng = np.random.default_rng(11 * sigma + hot)
+    lens = np.concatenate([np.tile([longest, 0, 3, 64, 129, 128, 1], 5),
+                           rng.integers(0, 30, 500), [longest, 0, 0]])
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    nc = 2048
+    col = (nc * rng.random(rp[-1]) ** 3).astype(np.int32)
+    vals = rng.uniform(-1, 1, rp[-1])
+    r, c, v = to_device(rp, col, vals, dtype, dev)
+    plan = pkg.Plan(r, c, v, nc, sigma=sigma, desc_bits=desc_bits, hot_columns=hot)
+    bufs = [torch.full((len(rp) - 1,), float("nan"), dtype=dtype, device=dev) for _ in range(2)]
+    plan.zero_boundary(bufs[0])
+    for it in range(3):
+        x64 = seeded_x(nc, 30 + it, dtype)
+        plan.spmv_dual(torch.from_numpy(x64).to(dtype).to(dev), bufs[it % 2], bufs[(it + 1) % 2])
+        torch.cuda.synchronize()
+        check_spmv(bufs[it % 2], rp, col, host_values(vals, dtype), x64, dtype, f"launch {it}")
+    plan.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=["f32", "f64"])
+@pytest.mark.parametrize("stripes,hot", [(0, 0), (0, 50), (8, 0), (8, 50)])
+@pytest.mark.parametrize("lanes,limit", [(0, 0), (0, 1), (256, 1), (512, 0)])
+def test_tiles_dealt_to_blocks(lanes, limit, stripes, hot, dtype):
+    """A block's wavefronts take its tiles from a counter in LDS: fewer tiles
+    than one block's wavefronts, a last block with one tile, grids of one block
+    per CU with several tiles per wavefront, and tile ranges that are empty or
+    hold fewer tiles than blocks; the counter starts anew in every launch."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    nc = 700
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for tiles in (1, 3, 4, 5, 17, 4 * cus + 1, 9 * cus - 1):
+        steps = 2 * OMEGA * tiles  # sigma 2
+        n = steps // 4
+        rng = np.random.default_rng(tiles)
+        rp = np.sort(np.concatenate([[0, steps - n], rng.integers(0, steps - n + 1, n - 1)]))
+        rp = rp.astype(np.int32)
+        col = (nc * rng.random(rp[-1]) ** 3).astype(np.int32)
+        vals = rng.uniform(-1, 1, rp[-1])
+        r, c, v = to_device(rp, col, vals, dtype, dev)
+        plan = pkg.Plan(r, c, v, nc, sigma=2, block_lanes=lanes, blocks_per_cu=limit,
+                        stripes=stripes, hot_columns=hot)
+        assert stripes or plan.info()["tile_num"] == tiles
+        y = torch.full((n,), float("nan"), dtype=dtype, device=dev)
+        for rep in range(2):
+            x64 = seeded_x(nc, 50 + rep, dtype)
+            plan.spmv(torch.from_numpy(x64).to(dtype).to(dev), out=y)
+            torch.cuda.synchronize()
+            check_spmv(y, rp, col, host_values(vals, dtype), x64, dtype, f"{tiles} tiles {rep}")
+        plan.close()
