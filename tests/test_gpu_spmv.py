@@ -606,3 +606,31 @@ def test_tiles_dealt_to_blocks(lanes, limit, stripes, hot, dtype):
             torch.cuda.synchronize()
             check_spmv(y, rp, col, host_values(vals, dtype), x64, dtype, f"{tiles} tiles {rep}")
         plan.close()
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local"])
+def test_no_plan_is_built_under_capture(mode):
+    """While a stream is captured device memory cannot be allocated: a plan is
+    refused also when the library keeps blocks of the sizes it needs, and the
+    plans there are go on working."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    rp, col, vals, nc = _matrix("chung_lu_10k", seed=9)
+    r, c, v = to_device(rp, col, vals, torch.float32, dev)
+    plan = pkg.Plan(r, c, v, nc)
+    pkg.Plan(r, c, v, nc, validate=False, hot_columns=0).close()  # its blocks are kept
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        graph.capture_begin(capture_error_mode=mode)
+        try:
+            with pytest.raises(pkg.MerbitError):
+                pkg.Plan(r, c, v, nc, validate=False, hot_columns=0)
+        finally:
+            with pytest.raises(RuntimeError):  # the refused allocation ended the capture
+                graph.capture_end()
+    x64 = seeded_x(nc, 5, torch.float32)
+    y = plan.spmv(torch.from_numpy(x64).float().to(dev))
+    torch.cuda.synchronize()
+    check_spmv(y, rp, col, host_values(vals, torch.float32), x64, torch.float32, "after")
+    plan.close()
