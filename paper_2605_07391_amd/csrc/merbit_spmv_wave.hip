@@ -86,13 +86,13 @@ constexpr bool kBufferStream = sizeof(V) == 4 || sizeof(D) == 8;
 // How a gather picks LDS (hot columns) or memory: one flat load from a selected
 // address, or a load from memory for every lane (hot ones repeat x[0]) and one
 // from LDS.  The flat load is faster (sigma 28 FP32 on R-MAT 22: 199 against
-// 203 us per SpMV; sigma 24 FP64 306 against 322) but for FP64 with 64-bit
-// descriptors of sigma 14 and 16 (305 against 285 us).  Written as a branch,
-// the compiler emits the flat load in some instances and in others a global
-// and an LDS load into one register, each waiting for the one before (sigma 16
-// FP32: 297 against 213 us).
+// 203 us per SpMV; FP64 sigma 24 306 against 322, sigma 14 300 against 312, on
+// R-MAT 20 75 against 77) but for FP64 with 64-bit descriptors of sigma 16 (306
+// against 285 us).  Written as a branch, the compiler emits the flat load in
+// some instances and in others a global and an LDS load into one register, each
+// waiting for the one before (sigma 16 FP32: 297 against 213 us).
 template <typename V, int SIGMA, typename D>
-constexpr bool kFlatGather = sizeof(V) == 4 || sizeof(D) == 4 || SIGMA > 16;
+constexpr bool kFlatGather = sizeof(V) == 4 || sizeof(D) == 4 || SIGMA != 16;
 
 // word 3 of a raw (unformatted, stride 0) buffer resource on gfx950
 constexpr int kBufferWord3 = 0x00020000;
