@@ -94,6 +94,7 @@ static SpmvArgs spmv_args(const merbit_plan* p, const void* x, void* y, void* z)
   a.chunks_per_block = p->chunks_per_block;
   a.grid = p->grid;
   a.hot_n = p->hot_n;
+  a.deal = p->deal;
   a.row_start = p->row_start;
   a.ranges = p->ranges;
   a.range_tile = p->range_tile;
@@ -217,6 +218,10 @@ static bool kernel_supported(const merbit_plan* p, bool hot) {
 
 // wavefronts per block of a wave plan without a hot cache (size_grid)
 constexpr int kPlainWaves = 4;
+// tiles per wavefront, and wavefronts per block, from which an FP64 plan deals
+// its blocks as many neighbouring tiles as they have wavefronts (size_grid)
+constexpr int64_t kDealMinTilesPerWave = 64;
+constexpr int kDealMinWaves = 8;
 
 // Choose the grid.  Block kernel: one commit unit (b lanes) per block, or with
 // the hot cache as many blocks as fit at once, each taking a run of units.
@@ -234,6 +239,14 @@ constexpr int kPlainWaves = 4;
 // blocks began 15 us into a 26 us launch).  SpMV FP32, blocks of 16 and of 4:
 // R-MAT 18 29.2 and 23.4 us, R-MAT 16 14.3 and 10.7, Chung-Lu 200,003 13.9 and
 // 9.9, 50,000 12.5 and 9.4.
+//
+// Neighbouring tiles share lines of x, so that dealt together to a block they
+// save gathers; dealt singly they balance the blocks.  FP64, single tiles and
+// runs of 8: R-MAT 22 (78 tiles per wavefront) 462 and 450 us, Chung-Lu
+// 8,000,003 x 10 (82) 583 and 571; R-MAT 21 (39) 175.7 and 179.6, R-MAT 20 (20)
+// 84.0 and 86.5, Chung-Lu 4,000,003 x 10 (41) 259 and 255, 2,000,003 x 10 (20)
+// 112 and 111, 700,001 x 12 (8) 45.4 and 46.5.  Runs of 4 in blocks of 4
+// wavefronts, R-MAT 22: 486 and 493.
 int size_grid(merbit_plan* p) {
   p->launch_waves = p->waves;
   if (p->commit == MERBIT_COMMIT_WAVE && p->stripes <= 1 && p->hot_n == 0 && !p->lanes_given &&
@@ -268,6 +281,9 @@ int size_grid(merbit_plan* p) {
   if (p->commit == MERBIT_COMMIT_WAVE) {
     const int64_t need = (p->tile_num + waves - 1) / waves;  // one tile per wavefront
     p->grid = (int)(grid < need ? grid : need);
+    if (p->dtype == MERBIT_F64 && p->desc_bits == 32 && p->stripes <= 1 && waves >= kDealMinWaves &&
+        p->tile_num >= kDealMinTilesPerWave * p->grid * waves)
+      p->deal = ceil_log2(waves);
     if (p->stripes > 1 && p->grid >= kXcds) {
       p->grid -= p->grid % kXcds;
       p->ranges = kXcds;

@@ -228,6 +228,7 @@ struct SpmvArgs {
   int32_t chunks_per_block;
   int32_t grid;
   int32_t hot_n;
+  int32_t deal;  // wave kernel, FP64 with 32-bit descriptors: blocks are dealt 2^deal tiles at a time
   // wave kernel, [tile_num + 1]: first nonzero of each tile's first row, -1 if
   // that row has more than kOwnRowMax nonzeros or crosses into another range
   // (0 after the last tile).  The

@@ -17,7 +17,7 @@
 //     tile zeroes z at its first row, Sec. 4.2 opt. (3)).
 // A block of WAVES wavefronts is resident for the whole launch.  The tiles
 // (with the tiles split into ranges, those of the block's range) are dealt
-// round robin over the blocks, and a block's wavefronts take the block's tiles
+// round robin over the blocks (singly, or in runs in a large FP64 plan), and a block's wavefronts take the block's tiles
 // one at a time from a counter in LDS.  The loads of the next tile (bounds,
 // descriptor, col_ind, values) are issued before the current tile's gathers
 // are consumed, so memory stays busy while a tile is walked and committed.
@@ -260,7 +260,9 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
   };
   auto tile_at = [&](int i) -> int {
     i = __builtin_amdgcn_readfirstlane(i);
-    const int tile = t_begin + i * slots + slot;
+    int tile = t_begin + i * slots + slot;
+    if constexpr (sizeof(V) == 8 && sizeof(D) == 4)  // runs of 2^deal tiles
+      tile = t_begin + (((i >> a.deal) * slots + slot) << a.deal) + (i & ((1 << a.deal) - 1));
     return tile < t_end ? tile : t_end;
   };
   // x of column c, or for a hot column (kFlatGather off) an x value that x_of

@@ -634,3 +634,33 @@ def test_no_plan_is_built_under_capture(mode):
     torch.cuda.synchronize()
     check_spmv(y, rp, col, host_values(vals, torch.float32), x64, torch.float32, "after")
     plan.close()
+
+
+@pytest.mark.parametrize("lanes", [256, 512, 1024])
+@pytest.mark.parametrize("more", [-1, 0, 1, 13])
+def test_large_fp64_plans_deal_runs_of_tiles(more, lanes):
+    """FP64 plans of at least 64 tiles per wavefront, in blocks of at least 8,
+    deal their blocks runs of neighbouring tiles: one tile below the line, at
+    it, and beyond it with a run that is cut short."""
+    import paper_2605_07391_amd as pkg
+    dev = require_gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = 64 * cus * (lanes // 64) + more
+    steps = OMEGA * tiles - 5  # sigma 1, the last tile not full
+    n, nc = steps // 5, 5000
+    rng = np.random.default_rng(lanes + more)
+    rp = np.sort(np.concatenate([[0, steps - n], rng.integers(0, steps - n + 1, n - 1)]))
+    rp = rp.astype(np.int32)
+    col = (nc * rng.random(rp[-1]) ** 3).astype(np.int32)
+    vals = rng.uniform(-1, 1, rp[-1])
+    r, c, v = to_device(rp, col, vals, torch.float64, dev)
+    plan = pkg.Plan(r, c, v, nc, sigma=1, block_lanes=lanes, blocks_per_cu=1, hot_columns=0)
+    info = plan.info()
+    assert info["tile_num"] == tiles and info["grid"] == cus
+    y = torch.full((n,), float("nan"), dtype=torch.float64, device=dev)
+    for rep in range(2):
+        x64 = seeded_x(nc, rep, torch.float64)
+        plan.spmv(torch.from_numpy(x64).to(dev), out=y)
+        torch.cuda.synchronize()
+        check_spmv(y, rp, col, vals, x64, torch.float64, f"{tiles} tiles")
+    plan.close()
