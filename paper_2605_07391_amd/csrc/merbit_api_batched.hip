@@ -273,8 +273,8 @@ int merbit_pagerank_personalized(merbit_plan* p, double alpha, double tol, int m
                                static_cast<char*>(p->pbuf[0]) + vsize(p->dtype) * c0 * n, kk,
                                kk, st));
     }
-    p->ppr_zeroed = 0;
   }
+  p->ppr_zeroed = -1;  // not known if the loop fails on the way
   double host_sums[128];
   int t = 0;
   bool converged = false;
@@ -313,6 +313,7 @@ int merbit_pagerank_personalized(merbit_plan* p, double alpha, double tol, int m
       }
     }
   }
+  p->ppr_zeroed = 0;
   p->last_stream = st;
   if (convert)
     HIP_TRY(launch_ppr_from_slabs(p->dtype, xs[t & 1], X_inout, n, k, st));

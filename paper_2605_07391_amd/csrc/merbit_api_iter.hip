@@ -23,6 +23,7 @@ int pagerank_loop(merbit_plan* p, PageRankWork& w, double alpha, double tol, int
   // delta_0: per-block dangling mass of x_0 into partials[0]
   HIP_TRY(launch_dangling_sum(p->dtype, x_inout, w.dmask, n, w.partials[0], w.reduce_grid, st));
   int yb = w.zeroed_buf;
+  w.zeroed_buf = -1;  // not known if the loop fails on the way
   if (yb < 0) {
     yb = 0;
     rc = zero_boundary(p, w.ybuf[0], st);
@@ -115,6 +116,7 @@ int merbit_pagerank(merbit_plan* p, double alpha, double tol, int max_iter, int 
   w.dmask = p->dmask;
   w.reduce_grid = p->reduce_grid;
   w.zeroed_buf = p->zeroed_buf;
+  p->zeroed_buf = -1;
   w.graphs = true;
   w.timed = true;
   w.host_pairs = host_pairs.data();
@@ -232,6 +234,7 @@ int merbit_pagerank_multi(merbit_plan* p, const int64_t* graph_ptr, int n_graphs
 
   HIP_TRY(launch_multi_dangling(p->dtype, x_inout, p->dmask, mt, p->multi_gsum[0], st));
   int yb = p->zeroed_buf;
+  p->zeroed_buf = -1;  // not known if the loop fails on the way
   if (yb < 0) {
     yb = 0;
     rc = zero_boundary(p, p->ybuf[0], st);
@@ -321,6 +324,7 @@ int merbit_pagerank_adjoint(merbit_plan* p, merbit_plan* pt, double alpha, doubl
   const size_t vb = vsize(p->dtype) * (size_t)n;
   HIP_TRY(launch_adj_sum(p->dtype, lam_inout, n, pt->partials[0], pt->reduce_grid, st));
   int yb = pt->zeroed_buf;
+  pt->zeroed_buf = -1;  // not known if the loop fails on the way
   if (yb < 0) {
     yb = 0;
     const int rz = zero_boundary(pt, pt->ybuf[0], st);

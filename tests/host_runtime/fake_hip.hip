@@ -55,6 +55,8 @@ struct State {
   hipStream_t stream = nullptr;
   int fail_alloc = 0;  // 1: the next library allocation fails; n: the n-th
   int fail_sync = 0;   // the same for synchronisations
+  int fail_graph = 0;  // the same for graph instantiations
+  void* spmv_y = nullptr;  // what the last SpMV launch wrote
 };
 State& st() {
   static State* s = new State();
@@ -132,6 +134,8 @@ void fake_reset_log() {
 }
 const char* fake_log() { return st().log.c_str(); }
 void fake_fail_alloc(int n) { st().fail_alloc = n; }
+void fake_fail_graph(int n) { st().fail_graph = n; }
+void* fake_spmv_y() { return st().spmv_y; }
 void fake_fail_sync(int n) { st().fail_sync = n; }
 // returns what was left of the count before: > 0 if the failure did not come
 long fake_fail_new(long n) {
@@ -202,6 +206,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t, h
     }
     if (k.args[i].type == "merbit::SpmvArgs") {
       const merbit::SpmvArgs& a = *static_cast<const merbit::SpmvArgs*>(args[i]);
+      st().spmv_y = a.y;
       const void* p[] = {a.x, a.y, a.z, a.row_start};
       for (size_t j = 0; j < sizeof p / sizeof p[0]; ++j)
         if (p[j] == nullptr) line += " m" + std::to_string(j);
@@ -316,6 +321,7 @@ hipError_t hipStreamEndCapture(hipStream_t q, hipGraph_t* g) {
   return hipSuccess;
 }
 hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+  if (countdown(st().fail_graph)) return hipErrorOutOfMemory;
   *e = reinterpret_cast<hipGraphExec_t>(malloc(8));
   return hipSuccess;
 }

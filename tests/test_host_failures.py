@@ -57,6 +57,7 @@ def lib(tmp_path_factory):
         getattr(lib, f).restype = ctypes.c_long
     lib.fake_fail_new.argtypes, lib.fake_fail_new.restype = [ctypes.c_long], ctypes.c_long
     lib.fake_capture.argtypes = [vp, ctypes.c_int]
+    lib.fake_spmv_y.restype = vp
     lib.merbit_release_memory.restype = ctypes.c_int64
     lib.merbit_last_error.restype = ctypes.c_char_p
     lib.merbit_plan_destroy.restype = None
@@ -185,6 +186,40 @@ def test_personalized_pagerank_after_a_failed_allocation(lib, k, before_k):
     # two or three vectors, and on a new plan the mask and its work space, the
     # parts, two sums and the sources
     assert n == (3 if k == 64 else 2) + (0 if before_k else 6)
+
+
+@pytest.mark.parametrize("driver", ["pagerank", "multi", "adjoint", "personalized"])
+def test_output_buffers_after_a_loop_that_failed(lib, driver):
+    """A driver's two output buffers take turns at being zero where the next
+    product adds onto them; a call that fails between two chunks of its loop
+    leaves that unknown, and the next one clears a buffer first."""
+    D = ctypes.c_double
+    plan = HostPlan(lib, eager_loops=0)
+    x, g = np.ones(N, np.float32), np.ones(N, np.float32)
+    gp = np.array([0, 100, N], np.int64)
+    src, X = np.zeros(3, np.int32), np.ones((N, 3), np.float32)
+    clear = "spmm_zero" if driver == "personalized" else "zero_boundary"
+
+    def call(alpha):
+        if driver == "personalized":
+            return lib.merbit_pagerank_personalized(plan.h, D(alpha), D(0.0), 25, 5, _p(src), 3,
+                                                    _p(X), None, None, None)
+        if driver == "pagerank":
+            return lib.merbit_pagerank(plan.h, D(alpha), D(0.0), 25, 5, _p(x), None, None, None)
+        if driver == "multi":
+            return lib.merbit_pagerank_multi(plan.h, _p(gp), 2, D(alpha), D(0.0), 25, 5, _p(x),
+                                             None, None, None)
+        return lib.merbit_pagerank_adjoint(plan.h, plan.h, D(alpha), D(0.0), 25, 5, _p(g), _p(x),
+                                           None, None, None)
+
+    assert call(0.85) == mb.OK
+    rc, run = _launches(lib, lambda: call(0.85))
+    assert rc == mb.OK and not any(k.startswith(clear) for k, _ in run)
+    lib.fake_fail_graph(2)
+    assert call(0.5) == mb.ENOMEM  # the second chunk, after one of 5 steps
+    rc, run = _launches(lib, lambda: call(0.85))
+    assert rc == mb.OK and any(k.startswith(clear) for k, _ in run)
+    plan.close()
 
 
 def _tune(lib):
