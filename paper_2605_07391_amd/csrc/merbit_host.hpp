@@ -233,6 +233,8 @@ int run_chunk(merbit_plan* p, int kind, int parity, int ybuf, int len, int k,
   const int rc = enqueue(p->cap_stream);
   hipGraph_t graph = nullptr;
   const hipError_t e = hipStreamEndCapture(p->cap_stream, &graph);
+  const int sp_out = p->yv_cur;
+  p->yv_cur = sp_in;  // nothing has run yet
   if (rc != MERBIT_OK) {
     if (graph) (void)hipGraphDestroy(graph);
     return rc;
@@ -248,9 +250,10 @@ int run_chunk(merbit_plan* p, int kind, int parity, int ybuf, int len, int k,
     p->loop_graphs.erase(p->loop_graphs.begin());
   }
   p->loop_graphs.push_back(
-      {kind, parity, ybuf, len, k, sp_in, p->yv_cur, x, aux, alpha, p->generation, exec});
+      {kind, parity, ybuf, len, k, sp_in, sp_out, x, aux, alpha, p->generation, exec});
   ++p->graph_captures;
   HIP_TRY(hipGraphLaunch(exec, st));
+  p->yv_cur = sp_out;
   return MERBIT_OK;
 }
 

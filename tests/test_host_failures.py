@@ -222,6 +222,28 @@ def test_output_buffers_after_a_loop_that_failed(lib, driver):
     plan.close()
 
 
+def test_stacked_buffers_after_a_chunk_that_was_not_run(lib):
+    """A striped plan's two buffers of the stacked products take turns as well: a
+    chunk that was recorded and could not be instantiated has not used them."""
+    lib.fake_fill(1)
+    plan = HostPlan(lib, stripes=8, eager_loops=0)
+    lib.fake_fill(0)
+    assert plan.rc == mb.OK
+    x, y = np.ones(N, np.float32), np.ones(N, np.float32)
+
+    def buffer():
+        assert lib.merbit_spmv(plan.h, _p(x), _p(y), None) == mb.OK
+        return lib.fake_spmv_y()
+
+    first, second = buffer(), buffer()
+    assert first != second
+    lib.fake_fail_graph(1)
+    assert lib.merbit_pagerank(plan.h, ctypes.c_double(0.85), ctypes.c_double(0.0), 5, 5, _p(x),
+                               None, None, None) == mb.ENOMEM
+    assert buffer() == first
+    plan.close()
+
+
 def _tune(lib):
     rp, col, val = _csr()
     o = mb.Opts()
