@@ -358,8 +358,7 @@ hipError_t hipGetDevice(int* d) {
 }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
-  *v = a == hipDeviceAttributeMultiprocessorCount ? 256
-       : a == hipDeviceAttributeMaxSharedMemoryPerMultiprocessor ? 160 * 1024 : 0;
+  *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 160 * 1024;  // or LDS bytes
   return hipSuccess;
 }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int threads, size_t) {
