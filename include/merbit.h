@@ -54,8 +54,10 @@ typedef enum {
                                 tiles and committed after one block barrier; only the
                                 block's first and last rows are added atomically         */
     MERBIT_COMMIT_WAVE = 2   /* b = 64: every wavefront commits its own tile with no
-                                barrier; each tile's first and last rows are added
-                                atomically; blocks stay resident and stride over tiles  */
+                                barrier; a row of at most 128 nonzeros that crosses
+                                tiles is stored by the tile it ends in, a longer one
+                                (or one that crosses tile ranges) is added atomically by
+                                each; blocks stay resident and take tile after tile     */
 } merbit_commit;
 
 /* Plan options; merbit_opts_init fills the defaults (every field 0 except
@@ -76,12 +78,15 @@ typedef struct {
                               concentrate their nonzeros on few columns.  -1 = automatic
                               (wave commit only: largest cache that fits one block per
                               CU, kept only when the hot columns hold >= 20 % of the
-                              nonzeros and the plan has at least 15,360 merge-path
-                              steps per CU -- a smaller plan cannot amortise the copy
-                              into LDS; the block kernel gets none), 0 = off,
+                              nonzeros and, without column stripes, the plan has at
+                              least 15,360 merge-path steps per CU -- a smaller plan
+                              cannot amortise the copy into LDS; a striped plan keeps
+                              its ranges' caches at any size; the block kernel gets
+                              none), 0 = off,
                               k > 0 = at most k columns (MERBIT_EUNSUPPORTED if k values
                               do not fit in LDS).  With the cache the plan owns a
-                              recoded copy of col_ind (int32[nnz]) and each SpMV first
+                              recoded copy of col_ind (int32[nnz]: 4 bytes per nonzero
+                              and about 0.2 ms more of plan build) and each SpMV first
                               gathers the hot x values (one small launch); the sums and
                               their order are unchanged.                                */
     int32_t validate;      /* nonzero: check the CSR on the device first (one host
@@ -201,9 +206,10 @@ int merbit_plan_export(merbit_plan* plan, int32_t* tile_x, uint32_t* tile_y,
 /* y <- A x (Sec. 4.2, Algorithm "MERBIT SpMV"), overwriting y whatever it
  * held.  x: device [n_cols], y: device [n_rows], both of the plan's dtype, not
  * aliased.  Launches: a scatter that zeroes y at the first row of every commit
- * unit (not for a validated WAVE plan whose rows all have at most 128
- * nonzeros), the hot-value gather (partial hot cache only), then the fused
- * kernel. */
+ * unit (not for a validated WAVE plan whose rows all have at most 128 nonzeros,
+ * nor for a striped plan) and, with a partial hot cache, the hot-value gather --
+ * one launch where both are due --, then the fused kernel (and a striped plan's
+ * sum of each row's stripes). */
 int merbit_spmv(merbit_plan* plan, const void* x, void* y, void* stream);
 
 /* Dual-buffer form (Sec. 4.2, optimisation (3)): the fused launch only (plus

@@ -189,9 +189,15 @@ __device__ __forceinline__ void block_sum2(double& a, double& b) {
   }
 }
 
-// nonzeros of a row up to which the tile it ends in finishes it alone.  An
-// atomic pair per tile costs more than reading half such a row again: see
-// merbit_spmv_wave.hip.
+// nonzeros of a row up to which the tile it ends in finishes it alone: an
+// atomic pair per tile costs more than reading half such a row again.  SpMV at
+// limits of 0 / 32 / 64 / 128 / 256, us: FP64 Chung-Lu 700,001 48.4 / 45.5 /
+// 45.4 / 45.2 / 45.3, R-MAT 20 84.3 / 83.9 / 84.7 / 84.0 / 90.6, R-MAT 22 459 /
+// 459 / 463 / 462 / 473; FP32 R-MAT 20 58.9 / 59.1 / 59.0 / 59.3 / 61.7, R-MAT 22
+// on 8 stripes (sigma 28) 198 / 197 / 196 / 199 / 203, 256 graphs of degree 8
+// (sigma 28) 236 / 233 / 232 / 231 / 230.  Up to 128 nothing is lost, and a plan
+// whose rows are all below it needs no zeros before a launch (rows of 80, 1M of
+// them, FP64 392 -> 346); beyond two loads per lane it costs more than it saves.
 constexpr int kOwnRowMax = 128;
 
 struct PlanArgs {

@@ -22,8 +22,8 @@
 // The bound holds the blocks of a plan, transpose and product of R-MAT 20: 319
 // MiB (FP32), 324 (FP64), which take 1.00 ms per matrix with kept blocks and 1.22
 // ms with hipMalloc alone (R-MAT 18: 81 MiB, 0.49 and 0.7-0.9 ms; R-MAT 16: 16
-// MiB, 0.19 and 0.24-0.29 ms).  The age is that of about 20 such matrices (a plan
-// with its temporaries makes 25 calls), and a request takes a block up to a third
+// MiB, 0.19 and 0.24-0.29 ms).  The age is that of about 25 such matrices (a plan
+// and its transpose make 20 calls), and a request takes a block up to a third
 // larger, so that matrices whose sizes differ by that much share blocks.
 #include <list>
 #include <mutex>

@@ -20,7 +20,8 @@
 // round robin over the blocks (singly, or in runs in a large FP64 plan), and a block's wavefronts take the block's tiles
 // one at a time from a counter in LDS.  The loads of the next tile (bounds,
 // descriptor, col_ind, values) are issued before the current tile's gathers
-// are consumed, so memory stays busy while a tile is walked and committed.
+// are consumed, so that the two wait together (they lie under branches, so the
+// compiler waits for all of them before the walk).
 //
 // What bounds it: the x gathers (L1 misses in flight per CU times the latency
 // of L2) and, below about 10M nonzeros, the fixed costs (the copy of the hot
