@@ -94,7 +94,7 @@ static SpmvArgs spmv_args(const merbit_plan* p, const void* x, void* y, void* z)
   a.chunks_per_block = p->chunks_per_block;
   a.grid = p->grid;
   a.hot_n = p->hot_n;
-  a.deal = p->deal;
+  a.runs = p->runs;
   a.row_start = p->row_start;
   a.ranges = p->ranges;
   a.range_tile = p->range_tile;
@@ -218,10 +218,9 @@ static bool kernel_supported(const merbit_plan* p, bool hot) {
 
 // wavefronts per block of a wave plan without a hot cache (size_grid)
 constexpr int kPlainWaves = 4;
-// tiles per wavefront, and wavefronts per block, from which an FP64 plan deals
-// its blocks as many neighbouring tiles as they have wavefronts (size_grid)
-constexpr int64_t kDealMinTilesPerWave = 64;
-constexpr int kDealMinWaves = 8;
+// tiles per wavefront from which an FP64 plan with a hot cache deals its blocks
+// as many neighbouring tiles as they have wavefronts (size_grid)
+constexpr int64_t kRunsMinTilesPerWave = 64;
 
 // Choose the grid.  Block kernel: one commit unit (b lanes) per block, or with
 // the hot cache as many blocks as fit at once, each taking a run of units.
@@ -281,9 +280,8 @@ int size_grid(merbit_plan* p) {
   if (p->commit == MERBIT_COMMIT_WAVE) {
     const int64_t need = (p->tile_num + waves - 1) / waves;  // one tile per wavefront
     p->grid = (int)(grid < need ? grid : need);
-    if (p->dtype == MERBIT_F64 && p->desc_bits == 32 && p->stripes <= 1 && waves >= kDealMinWaves &&
-        p->tile_num >= kDealMinTilesPerWave * p->grid * waves)
-      p->deal = ceil_log2(waves);
+    p->runs = p->dtype == MERBIT_F64 && p->desc_bits == 32 && p->stripes <= 1 && p->hot_n > 0 &&
+              waves >= kRunsMinWaves && p->tile_num >= kRunsMinTilesPerWave * p->grid * waves;
     if (p->stripes > 1 && p->grid >= kXcds) {
       p->grid -= p->grid % kXcds;
       p->ranges = kXcds;

@@ -26,7 +26,7 @@ struct merbit_plan {
   int64_t chunk_num = 0;  // commit units
   int unit_tiles = 1;     // tiles per commit unit: 1 (wave) or waves (block)
   int grid = 0, chunks_per_block = 1;
-  int deal = 0;  // wave kernel: log2 of the tiles dealt to a block at a time
+  bool runs = false;  // wave kernel: blocks are dealt runs of neighbouring tiles
   int32_t* tile_x = nullptr;
   uint32_t* tile_y = nullptr;
   int32_t* row_start = nullptr;  // [tile_num + 1], wave commit (SpmvArgs)

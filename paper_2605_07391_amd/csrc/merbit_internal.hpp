@@ -200,6 +200,9 @@ __device__ __forceinline__ void block_sum2(double& a, double& b) {
 // them, FP64 392 -> 346); beyond two loads per lane it costs more than it saves.
 constexpr int kOwnRowMax = 128;
 
+// wavefronts per block from which the wave kernel is built to deal runs of tiles
+constexpr int kRunsMinWaves = 8;
+
 struct PlanArgs {
   const int32_t* row_ptr;
   int32_t n_rows;
@@ -234,7 +237,6 @@ struct SpmvArgs {
   int32_t chunks_per_block;
   int32_t grid;
   int32_t hot_n;
-  int32_t deal;  // wave kernel, FP64 with 32-bit descriptors: blocks are dealt 2^deal tiles at a time
   // wave kernel, [tile_num + 1]: first nonzero of each tile's first row, -1 if
   // that row has more than kOwnRowMax nonzeros or crosses into another range
   // (0 after the last tile).  The
@@ -248,6 +250,9 @@ struct SpmvArgs {
   int32_t ranges;
   const int32_t* range_tile;
   const int32_t* hot_off;
+  // wave kernel: nonzero: blocks are dealt runs of neighbouring tiles where the
+  // kernel is built for it (kHasRuns)
+  int32_t runs;
 };
 
 struct SpmmArgs {

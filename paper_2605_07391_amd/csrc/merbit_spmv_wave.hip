@@ -183,8 +183,25 @@ __device__ __forceinline__ void wave_load_tile(const SpmvArgs& a, const int32_t*
 // 8 / 20 steps.
 constexpr int kWalkGroup = 4;
 
-template <typename V, int SIGMA, int WAVES, bool HOT, typename D>
+// The kernel's descriptor argument: the word, or InRuns of it where the tiles
+// are dealt in runs of WAVES neighbours (SpmvArgs::runs).
+template <typename D>
+struct InRuns {};
+template <typename DESC>
+struct DescOf {
+  typedef DESC word;
+  static constexpr bool runs = false;
+};
+template <typename D>
+struct DescOf<InRuns<D>> {
+  typedef D word;
+  static constexpr bool runs = true;
+};
+
+template <typename V, int SIGMA, int WAVES, bool HOT, typename DESC>
 __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
+  typedef typename DescOf<DESC>::word D;
+  constexpr bool RUNS = DescOf<DESC>::runs;
   constexpr int BITS = ceil_log2(kOmega * SIGMA);
   constexpr uint32_t FMASK = (1u << BITS) - 1u;
   static_assert(2 * BITS + SIGMA <= 8 * (int)sizeof(D), "descriptor does not fit");
@@ -261,9 +278,8 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
   };
   auto tile_at = [&](int i) -> int {
     i = __builtin_amdgcn_readfirstlane(i);
-    int tile = t_begin + i * slots + slot;
-    if constexpr (sizeof(V) == 8 && sizeof(D) == 4)  // runs of 2^deal tiles
-      tile = t_begin + (((i >> a.deal) * slots + slot) << a.deal) + (i & ((1 << a.deal) - 1));
+    const int tile = RUNS ? t_begin + (i / WAVES * slots + slot) * WAVES + i % WAVES
+                          : t_begin + i * slots + slot;
     return tile < t_end ? tile : t_end;
   };
   // x of column c, or for a hot column (kFlatGather off) an x value that x_of
@@ -423,8 +439,20 @@ __global__ __launch_bounds__(WAVES * 64) void spmv_wave_kernel(SpmvArgs a) {
   }
 }
 
+// kernels that exist with runs: instances of their own, as the choice at run
+// time cost plans that deal single tiles (FP64 Chung-Lu 700,001 46.2 -> 46.4 us)
+template <typename V, int W, bool H, typename D>
+constexpr bool kHasRuns = sizeof(V) == 8 && sizeof(D) == 4 && H && W >= kRunsMinWaves;
+
 template <typename V, int S, int W, bool H, typename D>
 static hipError_t launch_wave_t(const SpmvArgs& a, size_t dyn, hipStream_t st) {
+  if constexpr (kHasRuns<V, W, H, D>) {
+    if (a.runs) {
+      hipLaunchKernelGGL((spmv_wave_kernel<V, S, W, H, InRuns<D>>), dim3((unsigned)a.grid),
+                         dim3(W * kOmega), dyn, st, a);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((spmv_wave_kernel<V, S, W, H, D>), dim3((unsigned)a.grid), dim3(W * kOmega),
                      dyn, st, a);
   return hipGetLastError();
@@ -434,8 +462,17 @@ template <typename V, int S, int W, bool H, typename D>
 static hipError_t set_wave_lds_t(size_t bytes) {
   static std::mutex mu;
   static size_t granted[kMaxLdsDevices] = {};
-  return raise_dynamic_lds(reinterpret_cast<const void*>(&spmv_wave_kernel<V, S, W, H, D>), bytes,
-                           mu, granted);
+  const hipError_t e = raise_dynamic_lds(
+      reinterpret_cast<const void*>(&spmv_wave_kernel<V, S, W, H, D>), bytes, mu, granted);
+  if constexpr (kHasRuns<V, W, H, D>) {
+    static std::mutex mu_runs;
+    static size_t granted_runs[kMaxLdsDevices] = {};
+    if (e == hipSuccess)
+      return raise_dynamic_lds(
+          reinterpret_cast<const void*>(&spmv_wave_kernel<V, S, W, H, InRuns<D>>), bytes, mu_runs,
+          granted_runs);
+  }
+  return e;
 }
 
 // resident blocks per CU without dynamic LDS

@@ -639,9 +639,9 @@ def test_no_plan_is_built_under_capture(mode):
 @pytest.mark.parametrize("lanes", [256, 512, 1024])
 @pytest.mark.parametrize("more", [-1, 0, 1, 13])
 def test_large_fp64_plans_deal_runs_of_tiles(more, lanes):
-    """FP64 plans of at least 64 tiles per wavefront, in blocks of at least 8,
-    deal their blocks runs of neighbouring tiles: one tile below the line, at
-    it, and beyond it with a run that is cut short."""
+    """FP64 plans of at least 64 tiles per wavefront, in blocks of at least 8 and
+    with a hot-column cache, deal their blocks runs of neighbouring tiles: one
+    tile below the line, at it, and beyond it with a run that is cut short."""
     import paper_2605_07391_amd as pkg
     dev = require_gpu()
     cus = torch.cuda.get_device_properties(0).multi_processor_count
@@ -654,9 +654,9 @@ def test_large_fp64_plans_deal_runs_of_tiles(more, lanes):
     col = (nc * rng.random(rp[-1]) ** 3).astype(np.int32)
     vals = rng.uniform(-1, 1, rp[-1])
     r, c, v = to_device(rp, col, vals, torch.float64, dev)
-    plan = pkg.Plan(r, c, v, nc, sigma=1, block_lanes=lanes, blocks_per_cu=1, hot_columns=0)
+    plan = pkg.Plan(r, c, v, nc, sigma=1, block_lanes=lanes, blocks_per_cu=1, hot_columns=200)
     info = plan.info()
-    assert info["tile_num"] == tiles and info["grid"] == cus
+    assert info["tile_num"] == tiles and info["grid"] == cus and info["hot_columns"] > 0
     y = torch.full((n,), float("nan"), dtype=torch.float64, device=dev)
     for rep in range(2):
         x64 = seeded_x(nc, rep, torch.float64)
